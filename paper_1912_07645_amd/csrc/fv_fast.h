@@ -1,0 +1,446 @@
+// fv_fast.h -- the face arithmetic of fv_physics.h for cells of ordinary magnitude, in fewer
+// instructions and with the same results, bit for bit.
+//
+// What bounds the stencil kernels is the issue of FP64 instructions, and half of a WENO3 + HLLC
+// face is division and square root: a division as the compiler expands it (operands scaled, two
+// Newton steps, a rounding step, fix-ups for every special operand) takes 61 cycles of a SIMD per
+// wavefront, a square root 86, a fused multiply-add about 5 and the reciprocal estimate 17
+// (measured, 8 wavefronts per SIMD). Three things are saved here:
+//   * no scaling and no fix-up: those only matter for operands near the ends of the exponent
+//     range, for zeros, infinities and NaN;
+//   * one reciprocal for several denominators: 1/d_i = (1/(d_1 d_2 ..)) times the other ones,
+//     then the last Newton step for each by itself. The rounding step q + (a - b q) y of every
+//     quotient stays, so each is correctly rounded as before;
+//   * exact rewriting: a factor of two moved through a product (fma(2t, q/2, x) = fma(t, q, x)),
+//     minimum and maximum as single instructions, the physical flux only of the side of the
+//     contact that the HLLC flux takes, selections made only where some lane needs them.
+// All of this holds while no intermediate result leaves the normal range. That is made certain
+// from two sides. Every cell that a face reads has to be "tame": each field zero or of magnitude
+// 2^-200 .. 2^50 (the kernels look at the cells when they load them). And the quantities formed
+// at a face that a division or a root depends on have to lie in the windows below; a face tells
+// whether they do (the functions here return it). A wavefront with a face that they do not hold
+// for, or whose cells are not tame, computes its faces with fv_physics.h instead.
+//
+// Measured with the whole step (SSP-RK; before and after): 2D 1024^2 WENO3 + HLLC, 16 steps,
+// 2144 -> 1986 us; 256 samples of 256^2, 4 steps, 7.57 -> 6.88 ms; multilevel MUSCL + HLL run
+// 55.7 -> 47.7 ms; 3D 200 x 161 x 130, 3 steps, 3.04 -> 2.81 ms; the face of the 2D kernel went
+// from 363 VALU instructions with 15 reciprocal or root estimates to 312 with 8.
+//
+// Bounds behind the windows: a difference or a combination of tame values is zero or at least
+// 2^-252 (one cancellation loses at most 52 bits); a WENO3 denominator lies in [2^-41, 2^212]
+// and the product of four of them in [2^-164, 2^848]; with density and squared sound speed in
+// [2^-100, 2^100], every speed is below 2^154 and every numerator is zero or above 2^-900, so
+// remainders a - b q (106 bits below a) never become subnormal.
+#pragma once
+
+#include "fv_physics.h"
+
+namespace fvk {
+
+constexpr int kTameLo = -200, kTameHi = 50;   // exponents, as frexp gives them
+
+// ---------------------------------------------------------------- quotients and roots
+
+// 1/d to 2^-48 (the hardware estimate is good to 2^-24.3, one Newton step).
+__device__ __forceinline__ double recip48(double d)
+{
+    const double y = __builtin_amdgcn_rcp(d);
+    return __builtin_fma(__builtin_fma(-d, y, 1.0), y, y);
+}
+
+// y[i] = 1/d[i] within half a unit in the last place (2^-97 before its rounding) for N
+// denominators whose product stays in the normal range, from one hardware reciprocal.
+//
+// The rounding step of a quotient then fails for one kind of operands only: a denominator whose
+// 53 bits are all ones, whose reciprocal 2^k (1 + 2^-53 + 2^-106) lies that little above the
+// middle of two numbers, under a numerator that is a power of two. One denominator by itself
+// gets it right, since the hardware estimate does (this is the sequence that a division
+// expands to). SHARP gets it right for several, with a cubic last step: one more operation each,
+// taken where both operands come from the same few values of a nearly uniform flow. A WENO3
+// denominator and its numerator, sums of squares of squares and products with them, meet it by
+// chance only (2^-104).
+template <int N, bool SHARP = false>
+__device__ __forceinline__ void recips(const double (&d)[N], double (&y)[N])
+{
+    if constexpr (N == 1) {
+        y[0] = recip48(d[0]);
+    } else if constexpr (N == 2) {
+        const double r = recip48(d[0] * d[1]);
+        y[0] = r * d[1];
+        y[1] = r * d[0];
+    } else {
+        static_assert(N == 4, "one, two or four denominators");
+        const double d01 = d[0] * d[1], d23 = d[2] * d[3];
+        const double r = recip48(d01 * d23);
+        const double r01 = r * d23, r23 = r * d01;
+        y[0] = r01 * d[1];
+        y[1] = r01 * d[0];
+        y[2] = r23 * d[3];
+        y[3] = r23 * d[2];
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        double e = __builtin_fma(-d[i], y[i], 1.0);
+        if constexpr (SHARP) e = __builtin_fma(e, e, e);
+        y[i] = __builtin_fma(e, y[i], y[i]);
+    }
+}
+
+// a/b correctly rounded, with y from recips().
+__device__ __forceinline__ double quotient(double a, double b, double y)
+{
+    const double q = a * y;
+    return __builtin_fma(__builtin_fma(-b, q, a), y, q);
+}
+
+// 1/b correctly rounded.
+__device__ __forceinline__ double inverse(double b)
+{
+    const double d[1] = {b};
+    double y[1];
+    recips(d, y);
+    return __builtin_fma(__builtin_fma(-b, y[0], 1.0), y[0], y[0]);
+}
+
+// sqrt(x) correctly rounded: Goldschmidt's iteration for the root g and half its reciprocal h
+// from the hardware estimate, then two corrections by the residual x - g^2.
+__device__ __forceinline__ double root(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y;
+    double h = 0.5 * y;
+    const double r = __builtin_fma(-h, g, 0.5);
+    g = __builtin_fma(g, r, g);
+    h = __builtin_fma(h, r, h);
+    g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
+    return __builtin_fma(__builtin_fma(-g, g, x), h, g);
+}
+
+// ---------------------------------------------------------------- windows
+
+// Running range of the high words of positive doubles (ordered like the doubles; a negative
+// value falls below every positive one, infinities and NaN above every finite one).
+struct HighRange {
+    int lo = 0x7fffffff, hi = 0;
+    __device__ __forceinline__ void add(double x)
+    {
+        const int h = __double2hiint(x);
+        lo = h < lo ? h : lo;
+        hi = h > hi ? h : hi;
+    }
+    // every value in [2^E0, 2^E1)
+    template <int E0, int E1>
+    __device__ __forceinline__ bool within() const
+    {
+        return lo >= ((1023 + E0) << 20) && hi < ((1023 + E1) << 20);
+    }
+};
+
+// x in [2^E0, 2^E1), or -x if NEG.
+template <int E0, int E1, bool NEG = false>
+__device__ __forceinline__ bool in_window(double x)
+{
+    const uint32_t h = (uint32_t)__double2hiint(x) - ((uint32_t)(1023 + E0) << 20) - (NEG ? 0x80000000u : 0u);
+    return h < ((uint32_t)(E1 - E0) << 20);
+}
+
+// Running exponents of the fields of loaded cells (a zero counts as exponent 0, as do
+// infinities and NaN, which `bits` catches).
+struct CellRange {
+    int lo = 0, hi = 0;
+    uint32_t bits = 0;
+    template <bool FINITE>
+    __device__ __forceinline__ void add(double v)
+    {
+        const int e = __builtin_amdgcn_frexp_exp(v);
+        lo = e < lo ? e : lo;
+        hi = e > hi ? e : hi;
+        if (FINITE) {
+            const uint32_t b = (uint32_t)__double2hiint(v) << 1;
+            bits = b > bits ? b : bits;
+        }
+    }
+    __device__ __forceinline__ bool tame() const
+    {
+        return lo > kTameLo && hi <= kTameHi && bits < 0xffe00000u;
+    }
+};
+
+// Minimum and maximum of finite values (single instructions).
+__device__ __forceinline__ double fmin1(double a, double b) { return __builtin_fmin(a, b); }
+__device__ __forceinline__ double fmax1(double a, double b) { return __builtin_fmax(a, b); }
+
+// ---------------------------------------------------------------- reconstruction
+
+// minmod of finite values: one of the two terms is always a zero.
+__device__ __forceinline__ double minmod_finite(double a, double b)
+{
+    return fmax1(fmin1(a, b), 0.0) + fmin1(fmax1(a, b), 0.0);
+}
+
+// Numerators and denominators of weno3(a, b, c) (left) and weno3(d, c, b) (right), both halved
+// where the written form has the factor two:
+// 2 t1 (b + c)/2 + t0 (3b - a)/2 = t1 (b + c) + (t0/2)(3b - a).
+__device__ __forceinline__ void weno3_terms(double a, double b, double c, double d, double& nL,
+                                            double& dL, double& nR, double& dR)
+{
+    const double dbc = c - b, dab = b - a, ddc = c - d;
+    double tbc = __builtin_fma(dbc, dbc, 1e-6);
+    tbc = tbc * tbc;
+    double tab = __builtin_fma(dab, dab, 1e-6);
+    tab = tab * tab;
+    double tdc = __builtin_fma(ddc, ddc, 1e-6);
+    tdc = tdc * tdc;
+    const double s = b + c, h = 0.5 * tbc;
+    nL = __builtin_fma(tab, s, h * __builtin_fma(3.0, b, -a));
+    nR = __builtin_fma(tdc, s, h * __builtin_fma(3.0, c, -d));
+    dL = __builtin_fma(2.0, tab, tbc);
+    dR = __builtin_fma(2.0, tdc, tbc);
+}
+
+// Left and right states of every field at a face from at(q, j), field q of cell i - 2 + j.
+// WENO3 takes the fields two at a time: four denominators share a reciprocal.
+template <int RECON, int NF, class Cells>
+__device__ __forceinline__ void reconstruct_tame(const Cells& at, double* UL, double* UR)
+{
+    if constexpr (RECON == REC_FIRST) {
+#pragma unroll
+        for (int q = 0; q < NF; ++q) {
+            UL[q] = at(q, 1);
+            UR[q] = at(q, 2);
+        }
+    } else if constexpr (RECON == REC_MUSCL) {
+#pragma unroll
+        for (int q = 0; q < NF; ++q) {
+            const double b = at(q, 1), c = at(q, 2), m = c - b;
+            UL[q] = __builtin_fma(0.5, minmod_finite(b - at(q, 0), m), b);
+            UR[q] = __builtin_fma(-0.5, minmod_finite(m, at(q, 3) - c), c);
+        }
+    } else if constexpr (RECON == REC_ENO2) {
+#pragma unroll
+        for (int q = 0; q < NF; ++q) reconstruct<REC_ENO2>(at(q, 0), at(q, 1), at(q, 2), at(q, 3), UL[q], UR[q]);
+    } else {
+#pragma unroll
+        for (int q = 0; q + 1 < NF; q += 2) {
+            double n[4], d[4], y[4];
+            weno3_terms(at(q, 0), at(q, 1), at(q, 2), at(q, 3), n[0], d[0], n[1], d[1]);
+            weno3_terms(at(q + 1, 0), at(q + 1, 1), at(q + 1, 2), at(q + 1, 3), n[2], d[2], n[3], d[3]);
+            recips(d, y);
+            UL[q] = quotient(n[0], d[0], y[0]);
+            UR[q] = quotient(n[1], d[1], y[1]);
+            UL[q + 1] = quotient(n[2], d[2], y[2]);
+            UR[q + 1] = quotient(n[3], d[3], y[3]);
+        }
+        if constexpr (NF % 2) {
+            constexpr int q = NF - 1;
+            double n[2], d[2], y[2];
+            weno3_terms(at(q, 0), at(q, 1), at(q, 2), at(q, 3), n[0], d[0], n[1], d[1]);
+            recips(d, y);
+            UL[q] = quotient(n[0], d[0], y[0]);
+            UR[q] = quotient(n[1], d[1], y[1]);
+        }
+    }
+}
+
+// ---------------------------------------------------------------- Euler
+
+// Primitives of both sides of a face. False unless densities and squared sound speeds are
+// positive and in [2^-100, 2^100).
+template <int DIM>
+__device__ __forceinline__ bool euler_prims(const double* UL, const double* UR, const Phys& ph,
+                                            EulerPrim<DIM>& wl, EulerPrim<DIM>& wr)
+{
+    wl.ir = inverse(UL[0]);
+    wr.ir = inverse(UR[0]);
+    double kl = 0.0, kr = 0.0;   // twice the kinetic energies
+#pragma unroll
+    for (int k = 0; k < DIM; ++k) {
+        wl.u[k] = UL[1 + k] * wl.ir;
+        wr.u[k] = UR[1 + k] * wr.ir;
+        kl = (k == 0) ? UL[1] * wl.u[0] : kl + (UL[1 + k] * wl.u[k]);
+        kr = (k == 0) ? UR[1] * wr.u[0] : kr + (UR[1 + k] * wr.u[k]);
+    }
+    wl.p = ph.gm1 * __builtin_fma(-0.5, kl, UL[DIM + 1]);
+    wr.p = ph.gm1 * __builtin_fma(-0.5, kr, UR[DIM + 1]);
+    const double xl = (ph.gamma * wl.p) * wl.ir, xr = (ph.gamma * wr.p) * wr.ir;
+    wl.c = root(xl);
+    wr.c = root(xr);
+    HighRange r;
+    r.add(UL[0]);
+    r.add(UR[0]);
+    r.add(xl);
+    r.add(xr);
+    return r.within<-100, 100>();
+}
+
+// Some lane of the wavefront has c.
+__device__ __forceinline__ bool any_lane(bool c) { return __ballot(c) != 0ull; }
+
+// HLL's combination of NF fields with physical fluxes FL, FR and speeds SL < SR.
+template <int NF>
+__device__ __forceinline__ bool hll_tame(const double* UL, const double* UR, const double* FL,
+                                         const double* FR, double SL, double SR, double* Fh)
+{
+    const double d[1] = {SR - SL};
+    double y[1];
+    recips(d, y);
+    const double slsr = SL * SR;
+#pragma unroll
+    for (int q = 0; q < NF; ++q)
+        Fh[q] = quotient(((SR * FL[q]) - (SL * FR[q])) + (slsr * (UR[q] - UL[q])), d[0], y[0]);
+    const bool takeL = (SL >= 0.0), takeR = (SR <= 0.0);
+    if (any_lane(takeL || takeR)) {
+#pragma unroll
+        for (int q = 0; q < NF; ++q) Fh[q] = takeL ? FL[q] : (takeR ? FR[q] : Fh[q]);
+    }
+    return in_window<-150, 155>(d[0]);
+}
+
+// The HLLC flux of euler_numflux. The side K that decides (the supersonic side, or the side of
+// the contact) is chosen first, and only its physical flux and star state are formed.
+template <int DIM>
+__device__ __forceinline__ bool hllc_tame(const double* UL, const double* UR, const EulerPrim<DIM>& wl,
+                                          const EulerPrim<DIM>& wr, int nd, double* Fh)
+{
+    constexpr int NF = DIM + 2;
+    const double uL = pick<DIM>(wl.u, nd), uR = pick<DIM>(wr.u, nd);
+    const double SL = fmin1(uL - wl.c, uR - wr.c);
+    const double SR = fmax1(uL + wl.c, uR + wr.c);
+    const double eL = SL - uL, eR = SR - uR;
+    const double DL = UL[0] * eL;
+    const double DR = UR[0] * eR;
+    const double num = (wr.p - wl.p) + __builtin_fma(pick<DIM>(UL + 1, nd), eL, -(pick<DIM>(UR + 1, nd) * eR));
+    const double den[1] = {DL - DR};
+    double y1[1];
+    recips(den, y1);
+    const double Ss = quotient(num, den[0], y1[0]);
+    const bool takeL = (SL >= 0.0), takeR = (SR <= 0.0);
+    const bool left = takeL || (!takeR && Ss >= 0.0);
+    const double SK = left ? SL : SR;
+    const double DK = left ? DL : DR;
+    const double uK = left ? uL : uR;
+    const double pK = left ? wl.p : wr.p;
+    const double irK = left ? wl.ir : wr.ir;
+    double UK[NF], vK[DIM];
+#pragma unroll
+    for (int q = 0; q < NF; ++q) UK[q] = left ? UL[q] : UR[q];
+#pragma unroll
+    for (int k = 0; k < DIM; ++k) vK[k] = (k == nd) ? uK : (left ? wl.u[k] : wr.u[k]);
+    double FK[NF];
+    FK[0] = pick<DIM>(UK + 1, nd);
+#pragma unroll
+    for (int k = 0; k < DIM; ++k) {
+        const double a = UK[1 + k] * uK;
+        FK[1 + k] = (k == nd) ? (a + pK) : a;
+    }
+    FK[DIM + 1] = (UK[DIM + 1] + pK) * uK;
+    const double d2[2] = {SK - Ss, DK};
+    double y2[2];
+    recips<2, true>(d2, y2);
+    const double f = quotient(DK, d2[0], y2[0]);
+    double Us[NF];
+    Us[0] = f;
+#pragma unroll
+    for (int k = 0; k < DIM; ++k) Us[1 + k] = (k == nd) ? (f * Ss) : (f * vK[k]);
+    Us[DIM + 1] = f * __builtin_fma(UK[DIM + 1], irK, (Ss - uK) * (Ss + quotient(pK, DK, y2[1])));
+#pragma unroll
+    for (int q = 0; q < NF; ++q) Fh[q] = __builtin_fma(SK, Us[q] - UK[q], FK[q]);
+    if (any_lane(takeL || takeR)) {
+#pragma unroll
+        for (int q = 0; q < NF; ++q) Fh[q] = (takeL || takeR) ? FK[q] : Fh[q];
+    }
+    return in_window<-60, 300, true>(den[0]) && in_window<-300, 300>(d2[0] * d2[1]);
+}
+
+// Numerical flux at a face from tame cells; false where the windows do not hold.
+template <int DIM, int EQ, int FLUX>
+__device__ __forceinline__ bool numflux_tame(const double* UL, const double* UR, int nd, double* Fh,
+                                             const Phys& ph)
+{
+    if constexpr (EQ == EQ_EULER && (FLUX == FLUX_RUSANOV || FLUX == FLUX_HLL || FLUX == FLUX_HLLC)) {
+        constexpr int NF = DIM + 2;
+        EulerPrim<DIM> wl, wr;
+        const bool ok = euler_prims<DIM>(UL, UR, ph, wl, wr);
+        if constexpr (FLUX == FLUX_HLLC) {
+            return hllc_tame<DIM>(UL, UR, wl, wr, nd, Fh) && ok;
+        } else {
+            double FL[NF], FR[NF];
+            euler_flux<DIM>(UL, wl, nd, FL);
+            euler_flux<DIM>(UR, wr, nd, FR);
+            const double uL = pick<DIM>(wl.u, nd), uR = pick<DIM>(wr.u, nd);
+            if constexpr (FLUX == FLUX_RUSANOV) {
+                const double s = fmax1(fabs(uL) + wl.c, fabs(uR) + wr.c);
+#pragma unroll
+                for (int q = 0; q < NF; ++q) Fh[q] = 0.5 * ((FL[q] + FR[q]) - (s * (UR[q] - UL[q])));
+                return ok;
+            } else {
+                const double SL = fmin1(uL - wl.c, uR - wr.c);
+                const double SR = fmax1(uL + wl.c, uR + wr.c);
+                return hll_tame<NF>(UL, UR, FL, FR, SL, SR, Fh) && ok;
+            }
+        }
+    } else {
+        numflux<DIM, EQ, FLUX>(UL, UR, nd, Fh, ph);
+        return true;
+    }
+}
+
+// ---------------------------------------------------------------- one face
+
+// Whether faces of this scheme have a shorter form for tame cells.
+template <int EQ, int RECON, int FLUX>
+constexpr bool has_tame_face()
+{
+    if (RECON == REC_CELLS4) return false;
+    return RECON == REC_WENO3 || RECON == REC_MUSCL ||
+           (EQ == EQ_EULER && (FLUX == FLUX_RUSANOV || FLUX == FLUX_HLL || FLUX == FLUX_HLLC));
+}
+
+// Whether a cell that is not finite has to be seen when it is loaded. With Euler's windowed
+// fluxes a NaN reaches the density or the squared sound speed of the face (from the conserved
+// fields, or through the reciprocal that WENO3's fields share) and fails the window there.
+// minmod's minimum and maximum drop a NaN, and the other fluxes have no window on every field.
+template <int EQ, int RECON, int FLUX>
+constexpr bool cells_need_finite()
+{
+    return RECON == REC_MUSCL ||
+           !(EQ == EQ_EULER && (FLUX == FLUX_RUSANOV || FLUX == FLUX_HLL || FLUX == FLUX_HLLC));
+}
+
+// The cells around a face in LDS: field q of cell i - 2 + j at s[q * QS + (j - 2) * STRIDE].
+template <int QS, int STRIDE>
+struct LdsCells {
+    const double* su;
+    int c;
+    __device__ __forceinline__ double operator()(int q, int j) const { return su[q * QS + c + (j - 2) * STRIDE]; }
+    // read again from here on: values loaded before are not kept in registers for later
+    __device__ __forceinline__ void reload() { asm volatile("" : "+v"(c)); }
+};
+
+// Flux at the face with normal axis ND between cells i - 1 and i; at(q, j): field q of cell
+// i - 2 + j (j = 1, 2 only for first order). tame: uniform over the wavefront.
+template <int DIM, int EQ, int RECON, int FLUX, int ND, class Cells>
+__device__ __forceinline__ void face_flux(Cells at, const Phys& ph, bool tame, double* F)
+{
+    constexpr int NF = NumFields<DIM, EQ>::value;
+    if constexpr (has_tame_face<EQ, RECON, FLUX>()) {
+        if (tame) {
+            double UL[NF], UR[NF];
+            reconstruct_tame<RECON, NF>(at, UL, UR);
+            const bool ok = numflux_tame<DIM, EQ, FLUX>(UL, UR, ND, F, ph);
+            if (!any_lane(!ok)) return;
+        }
+        at.reload();
+    }
+    double UL[NF], UR[NF];
+#pragma unroll
+    for (int q = 0; q < NF; ++q) {
+        if constexpr (RECON == REC_FIRST)
+            reconstruct<RECON>(0.0, at(q, 1), at(q, 2), 0.0, UL[q], UR[q]);
+        else
+            reconstruct<RECON>(at(q, 0), at(q, 1), at(q, 2), at(q, 3), UL[q], UR[q]);
+    }
+    numflux<DIM, EQ, FLUX>(UL, UR, ND, F, ph);
+}
+
+}  // namespace fvk

@@ -19,7 +19,7 @@
 //      on the bit pattern (exact and order-independent), and non-physical cells are flagged.
 #pragma once
 
-#include "fv_physics.h"
+#include "fv_fast.h"
 
 namespace fvk {
 
@@ -100,10 +100,10 @@ struct TileLayout {
 };
 
 // One face with normal axis ND (compile-time): reconstruction from the LDS tile and the
-// numerical flux into F.
+// numerical flux into F. tame: every cell of the tile is (fv_fast.h).
 template <int DIM, int EQ, int RECON, int FLUX, int BX, int BY, int BZ, int NT, int ND,
           int LAY = LAY_FIELD>
-__device__ __forceinline__ void one_face(const double* su, const Phys& ph, int l, double* F)
+__device__ __forceinline__ void one_face(const double* su, const Phys& ph, bool tame, int l, double* F)
 {
     using T = StageTile<DIM, EQ, RECON, BX, BY, BZ, NT>;
     using TL = TileLayout<T::NF, T::PX, T::PY, T::PZ, LAY>;
@@ -129,17 +129,7 @@ __device__ __forceinline__ void one_face(const double* su, const Phys& ph, int l
         }
         ec4_face<DIM, EQ>(A, B, C, D, ND, F, ph);
     } else {
-        double UL[NF], UR[NF];
-#pragma unroll
-        for (int q = 0; q < NF; ++q) {
-            const double* s = su + q * TL::QS + c;
-            if (RECON == REC_FIRST) {
-                reconstruct<RECON>(0.0, s[-STRIDE], s[0], 0.0, UL[q], UR[q]);
-            } else {
-                reconstruct<RECON>(s[-2 * STRIDE], s[-STRIDE], s[0], s[STRIDE], UL[q], UR[q]);
-            }
-        }
-        numflux<DIM, EQ, FLUX>(UL, UR, ND, F, ph);
+        face_flux<DIM, EQ, RECON, FLUX, ND>(LdsCells<TL::QS, STRIDE>{su, c}, ph, tame, F);
     }
 }
 
@@ -184,8 +174,8 @@ struct SplitFaces {
 // Face pf of the padded list: F gets its flux, *slot its index in the unpadded list sf[q][f]
 // (-1 for padding; padding lanes recompute a valid face and store nothing).
 template <int DIM, int EQ, int RECON, int FLUX, int BX, int BY, int BZ, int NT>
-__device__ __forceinline__ void list_face(const double* su, const Phys& ph, int pf, double* F,
-                                          int* slot)
+__device__ __forceinline__ void list_face(const double* su, const Phys& ph, bool tame, int pf,
+                                          double* F, int* slot)
 {
     using T = StageTile<DIM, EQ, RECON, BX, BY, BZ, NT>;
     using L = FaceList<DIM, EQ, RECON, BX, BY, BZ, NT>;
@@ -194,17 +184,17 @@ __device__ __forceinline__ void list_face(const double* su, const Phys& ph, int 
     if (wave_first < L::PXN) {
         const int l = pf;
         const bool ok = l < NFX;
-        one_face<DIM, EQ, RECON, FLUX, BX, BY, BZ, NT, 0>(su, ph, ok ? l : NFX - 1, F);
+        one_face<DIM, EQ, RECON, FLUX, BX, BY, BZ, NT, 0>(su, ph, tame, ok ? l : NFX - 1, F);
         *slot = ok ? l : -1;
     } else if (DIM >= 2 && wave_first < L::PXN + L::PYN) {
         const int l = pf - L::PXN;
         const bool ok = l < NFY;
-        one_face<DIM, EQ, RECON, FLUX, BX, BY, BZ, NT, (DIM >= 2 ? 1 : 0)>(su, ph, ok ? l : NFY - 1, F);
+        one_face<DIM, EQ, RECON, FLUX, BX, BY, BZ, NT, (DIM >= 2 ? 1 : 0)>(su, ph, tame, ok ? l : NFY - 1, F);
         *slot = ok ? NFX + l : -1;
     } else {
         const int l = pf - L::PXN - L::PYN;
         const bool ok = DIM >= 3 && l < NFZ;
-        one_face<DIM, EQ, RECON, FLUX, BX, BY, BZ, NT, (DIM >= 3 ? 2 : 0)>(su, ph, ok ? l : (NFZ > 0 ? NFZ - 1 : 0), F);
+        one_face<DIM, EQ, RECON, FLUX, BX, BY, BZ, NT, (DIM >= 3 ? 2 : 0)>(su, ph, tame, ok ? l : (NFZ > 0 ? NFZ - 1 : 0), F);
         *slot = ok ? NFX + NFY + l : -1;
     }
 }
@@ -216,7 +206,7 @@ __device__ __forceinline__ void list_face(const double* su, const Phys& ph, int 
 // needs max(state tile, faces) of LDS instead of their sum, so more workgroups fit a CU.
 // HOLD = 2: y faces, then x faces written over the dead y halo rows (SplitFaces).
 template <int DIM, int EQ, int RECON, int FLUX, int BX, int BY, int BZ, int NT, int HOLD>
-__device__ __forceinline__ void tile_faces(const double* su, double* sf, const Phys& ph)
+__device__ __forceinline__ void tile_faces(const double* su, double* sf, const Phys& ph, bool tame)
 {
     using T = StageTile<DIM, EQ, RECON, BX, BY, BZ, NT>;
     using L = FaceList<DIM, EQ, RECON, BX, BY, BZ, NT>;
@@ -228,7 +218,7 @@ __device__ __forceinline__ void tile_faces(const double* su, double* sf, const P
         static_assert(NF * NFX >= S::LOW && S::YB >= S::SU, "x fluxes cover the low halo rows");
         for (int pf = threadIdx.x; pf < L::PYN; pf += NT) {
             double F[NF];
-            one_face<DIM, EQ, RECON, FLUX, BX, BY, BZ, NT, 1, LAY_ROW>(su, ph, pf < NFY ? pf : NFY - 1, F);
+            one_face<DIM, EQ, RECON, FLUX, BX, BY, BZ, NT, 1, LAY_ROW>(su, ph, tame, pf < NFY ? pf : NFY - 1, F);
             if (pf < NFY) {
 #pragma unroll
                 for (int q = 0; q < NF; ++q) sf[S::YB + q * NFY + pf] = F[q];
@@ -237,7 +227,7 @@ __device__ __forceinline__ void tile_faces(const double* su, double* sf, const P
         __syncthreads();   // the y halo rows are dead from here on
         for (int pf = threadIdx.x; pf < L::PXN; pf += NT) {
             double F[NF];
-            one_face<DIM, EQ, RECON, FLUX, BX, BY, BZ, NT, 0, LAY_ROW>(su, ph, pf < NFX ? pf : NFX - 1, F);
+            one_face<DIM, EQ, RECON, FLUX, BX, BY, BZ, NT, 0, LAY_ROW>(su, ph, tame, pf < NFX ? pf : NFX - 1, F);
             if (pf < NFX) {
 #pragma unroll
                 for (int q = 0; q < NF; ++q) sf[S::x_at(q, pf)] = F[q];
@@ -247,7 +237,7 @@ __device__ __forceinline__ void tile_faces(const double* su, double* sf, const P
         for (int pf = threadIdx.x; pf < L::TOTAL; pf += NT) {
             double F[NF];
             int slot;
-            list_face<DIM, EQ, RECON, FLUX, BX, BY, BZ, NT>(su, ph, pf, F, &slot);
+            list_face<DIM, EQ, RECON, FLUX, BX, BY, BZ, NT>(su, ph, tame, pf, F, &slot);
             if (slot >= 0) {
 #pragma unroll
                 for (int q = 0; q < NF; ++q) sf[q * NFACES + slot] = F[q];
@@ -260,7 +250,7 @@ __device__ __forceinline__ void tile_faces(const double* su, double* sf, const P
         for (int k = 0; k < L::FPT; ++k) {
             const int pf = threadIdx.x + k * NT;
             slot[k] = -1;
-            if (pf < L::TOTAL) list_face<DIM, EQ, RECON, FLUX, BX, BY, BZ, NT>(su, ph, pf, F[k], &slot[k]);
+            if (pf < L::TOTAL) list_face<DIM, EQ, RECON, FLUX, BX, BY, BZ, NT>(su, ph, tame, pf, F[k], &slot[k]);
         }
         __syncthreads();   // the state tile is dead from here on
 #pragma unroll
@@ -336,6 +326,8 @@ stage_kernel(const StageArgs args)
     using S = SplitFaces<DIM, EQ, RECON, BX, BY, BZ, NT>;
     constexpr int LDS = (HOLD == 1) ? (SU > SF ? SU : SF) : ((HOLD == 2) ? S::LDS : SU + SF);
     __shared__ double lds[LDS];
+    __shared__ int wild[NT / 64];   // per wavefront: it loaded a cell that is not tame
+    constexpr bool TAME = has_tame_face<EQ, RECON, FLUX>();
     double* su = lds;
     double* sf = (HOLD != 0) ? lds : lds + SU;
 
@@ -421,10 +413,16 @@ stage_kernel(const StageArgs args)
                 }
             }
         }
+        CellRange range;
 #pragma unroll
         for (int k = 0; k < LPT; ++k) {
             const int e = threadIdx.x + k * NT;
             if ((k + 1) * NT <= PCELLS || e < PCELLS) {
+                if constexpr (TAME) {
+#pragma unroll
+                    for (int q = 0; q < NF; ++q)
+                        range.add<cells_need_finite<EQ, RECON, FLUX>()>(v[k][q]);
+                }
                 const int px = e % PX;
                 const int row = e / PX;   // z * PY + y
 #pragma unroll
@@ -432,11 +430,22 @@ stage_kernel(const StageArgs args)
                     su[(LAY == LAY_FIELD) ? q * PCELLS + e : row * TL::RS + q * TL::QS + px] = v[k][q];
             }
         }
+        if constexpr (TAME) {
+            const bool any = any_lane(!range.tame());
+            if ((threadIdx.x & 63) == 0) wild[threadIdx.x >> 6] = any;
+        }
     }
     __syncthreads();
+    bool tame = false;
+    if constexpr (TAME) {
+        int w = 0;
+#pragma unroll
+        for (int i = 0; i < NT / 64; ++i) w |= wild[i];
+        tame = __builtin_amdgcn_readfirstlane(w) == 0;
+    }
 
     // 2. every face of the tile, once
-    tile_faces<DIM, EQ, RECON, FLUX, BX, BY, BZ, NT, HOLD>(su, sf, g.ph);
+    tile_faces<DIM, EQ, RECON, FLUX, BX, BY, BZ, NT, HOLD>(su, sf, g.ph, tame);
     __syncthreads();
 
     // 3 + 4. divergence and Runge--Kutta stage combination

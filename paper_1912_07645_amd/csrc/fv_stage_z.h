@@ -61,9 +61,10 @@ __device__ __forceinline__ void z_halo_pos(int h, int& px, int& py)
     }
 }
 
-// One x (ND = 0) or y (ND = 1) face of the plane: reconstruction from LDS and flux.
+// One x (ND = 0) or y (ND = 1) face of the plane: reconstruction from LDS and flux. tame: every
+// cell of the plane is (fv_fast.h).
 template <int EQ, int RECON, int FLUX, int BX, int BY, int NT, int ND>
-__device__ __forceinline__ void z_plane_face(const double* sp, const Phys& ph, int l, double* F)
+__device__ __forceinline__ void z_plane_face(const double* sp, const Phys& ph, bool tame, int l, double* F)
 {
     static_assert(FLUX != FLUX_EC4, "the z-marching kernel has no fourth-order EC path");
     using T = ZTile<EQ, RECON, BX, BY, NT>;
@@ -73,33 +74,21 @@ __device__ __forceinline__ void z_plane_face(const double* sp, const Phys& ph, i
     const int fx = l % EX;
     const int fy = l / EX;
     const int c = (fy + G) * PX + (fx + G);
-    double UL[NF], UR[NF];
-#pragma unroll
-    for (int q = 0; q < NF; ++q) {
-        const double* s = sp + q * PP + c;
-        if (RECON == REC_FIRST) {
-            reconstruct<RECON>(0.0, s[-STRIDE], s[0], 0.0, UL[q], UR[q]);
-        } else {
-            reconstruct<RECON>(s[-2 * STRIDE], s[-STRIDE], s[0], s[STRIDE], UL[q], UR[q]);
-        }
-    }
-    numflux<3, EQ, FLUX>(UL, UR, ND, F, ph);
+    face_flux<3, EQ, RECON, FLUX, ND>(LdsCells<PP, STRIDE>{sp, c}, ph, tame, F);
 }
 
 // The z face above the window's middle: w[0..2G-1] are the column's cells k-G+1 .. k+G.
+template <int NF, int G>
+struct WindowCells {
+    const double (&w)[2 * G][NF];
+    __device__ __forceinline__ double operator()(int q, int j) const { return w[j - 2 + G][q]; }
+    __device__ __forceinline__ void reload() {}
+};
+
 template <int EQ, int RECON, int FLUX, int NF, int G>
-__device__ __forceinline__ void z_column_face(const double (&w)[2 * G][NF], const Phys& ph, double* F)
+__device__ __forceinline__ void z_column_face(const double (&w)[2 * G][NF], const Phys& ph, bool tame, double* F)
 {
-    double UL[NF], UR[NF];
-#pragma unroll
-    for (int q = 0; q < NF; ++q) {
-        if (RECON == REC_FIRST) {
-            reconstruct<RECON>(0.0, w[0][q], w[1][q], 0.0, UL[q], UR[q]);
-        } else {
-            reconstruct<RECON>(w[0][q], w[1][q], w[2][q], w[3][q], UL[q], UR[q]);
-        }
-    }
-    numflux<3, EQ, FLUX>(UL, UR, 2, F, ph);
+    face_flux<3, EQ, RECON, FLUX, 2>(WindowCells<NF, G>{w}, ph, tame, F);
 }
 
 // WPE: the fewest wavefronts per SIMD to compile for. The column registers make this kernel
@@ -114,6 +103,9 @@ stage_kernel_z(const StageArgs args)
     constexpr int NFX = T::NFX, NFXY = T::NFXY;
     __shared__ double sp[NF * PP];     // current plane with its x and y halo
     __shared__ double sf[NF * NFXY];   // x faces, then y faces, of the current plane
+    __shared__ int wild;               // a cell that is not tame was staged
+    constexpr bool TAME = has_tame_face<EQ, RECON, FLUX>();
+    constexpr bool FIN = cells_need_finite<EQ, RECON, FLUX>();
 
     const int64_t blk = xcd_remap(blockIdx.x, args.nblocks);
     const int gi = find_group(args.g, args.ngroups, blk);
@@ -166,8 +158,17 @@ stage_kernel_z(const StageArgs args)
 #pragma unroll
         for (int q = 0; q < NF; ++q) hreg[q] = src[q * cells + hc];
     }
+    CellRange range;   // of the cells this thread has loaded
+    if constexpr (TAME) {
+        if (t == 0) wild = 0;
+#pragma unroll
+        for (int j = 0; j < 2 * G; ++j)
+#pragma unroll
+            for (int q = 0; q < NF; ++q) range.add<FIN>(w[j][q]);
+        __syncthreads();
+    }
     double fzm[NF];   // z flux on the lower face of the current plane
-    z_column_face<EQ, RECON, FLUX, NF, G>(w, g.ph, fzm);
+    z_column_face<EQ, RECON, FLUX, NF, G>(w, g.ph, TAME && !any_lane(!range.tame()), fzm);
 #pragma unroll
     for (int j = 0; j + 1 < 2 * G; ++j)
 #pragma unroll
@@ -188,6 +189,13 @@ stage_kernel_z(const StageArgs args)
         if (t < NH) {
 #pragma unroll
             for (int q = 0; q < NF; ++q) sp[q * PP + lhalo] = hreg[q];
+            if constexpr (TAME) {
+#pragma unroll
+                for (int q = 0; q < NF; ++q) range.add<FIN>(hreg[q]);
+            }
+        }
+        if constexpr (TAME) {
+            if (!range.tame()) wild = 1;
         }
         // 2. request the column cell k + G, the halo of plane k + 1 and (compiled for 3
         //    wavefronts per SIMD, where the registers are there) U^n of the updated cell
@@ -208,6 +216,7 @@ stage_kernel_z(const StageArgs args)
             for (int q = 0; q < NF; ++q) unr[q] = un[q * cells + cc];
         }
         __syncthreads();
+        const bool tame = TAME && __builtin_amdgcn_readfirstlane(wild) == 0;
 
         // 3. x and y faces of the plane (each axis padded to whole wavefronts)
 #pragma unroll
@@ -219,12 +228,12 @@ stage_kernel_z(const StageArgs args)
                 int slot;
                 if (wave_first < T::PXN) {
                     const bool ok = pf < NFX;
-                    z_plane_face<EQ, RECON, FLUX, BX, BY, NT, 0>(sp, g.ph, ok ? pf : NFX - 1, F);
+                    z_plane_face<EQ, RECON, FLUX, BX, BY, NT, 0>(sp, g.ph, tame, ok ? pf : NFX - 1, F);
                     slot = ok ? pf : -1;
                 } else {
                     const int l = pf - T::PXN;
                     const bool ok = l < T::NFY;
-                    z_plane_face<EQ, RECON, FLUX, BX, BY, NT, 1>(sp, g.ph, ok ? l : T::NFY - 1, F);
+                    z_plane_face<EQ, RECON, FLUX, BX, BY, NT, 1>(sp, g.ph, tame, ok ? l : T::NFY - 1, F);
                     slot = ok ? NFX + l : -1;
                 }
                 if (slot >= 0) {
@@ -235,7 +244,11 @@ stage_kernel_z(const StageArgs args)
         }
         // 4. the z face above plane k, in registers
         double fzp[NF];
-        z_column_face<EQ, RECON, FLUX, NF, G>(w, g.ph, fzp);
+        if constexpr (TAME) {
+#pragma unroll
+            for (int q = 0; q < NF; ++q) range.add<FIN>(w[2 * G - 1][q]);
+        }
+        z_column_face<EQ, RECON, FLUX, NF, G>(w, g.ph, TAME && !any_lane(!range.tame()), fzp);
         __syncthreads();
 
         // 5. divergence (x, y, z) and the Runge--Kutta stage combination
