@@ -83,6 +83,7 @@ static Group stage_group(const fv_adjoint* a, const double* src, const double* u
         g.tiles[k] = (int32_t)((s->grid.n[k] + tb[k] - 1) / tb[k]);
         g.ntiles *= g.tiles[k];
     }
+    set_divisors(g, g.tiles);
     g.batch = (int32_t)a->batch;
     g.block0 = 0;
     g.ph = s->ph;

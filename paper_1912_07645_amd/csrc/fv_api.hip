@@ -338,7 +338,7 @@ struct GroupRun {
     char* ws;
 };
 
-static Group make_group(const GroupRun& r, int stage)
+static Group make_group(const GroupRun& r, int stage, const StageKernel* kern)
 {
     const fv_solver* s = r.s;
     Group g{};
@@ -360,13 +360,14 @@ static Group make_group(const GroupRun& r, int stage)
     g.mbits = (unsigned long long*)(r.ws + r.L.mbits);
     g.bad = (int32_t*)(r.ws + r.L.bad);
     g.cells = s->cells;
-    const int32_t tb[3] = {s->kern->bx, s->kern->by, s->kern->bz};
+    const int32_t tb[3] = {kern->bx, kern->by, kern->bz};
     g.ntiles = 1;
     for (int k = 0; k < 3; ++k) {
         g.n[k] = (int32_t)s->grid.n[k];
         g.tiles[k] = (int32_t)((s->grid.n[k] + tb[k] - 1) / tb[k]);
         g.ntiles *= g.tiles[k];
     }
+    set_divisors(g, g.tiles);
     g.batch = (int32_t)r.batch;
     g.ph = s->ph;
     return g;
@@ -407,7 +408,7 @@ static StepPlan make_plan(std::vector<GroupRun>& runs)
         a.ngroups = (int32_t)runs.size();
         int64_t blocks = 0;
         for (size_t i = 0; i < runs.size(); ++i) {
-            a.g[i] = make_group(runs[i], st);
+            a.g[i] = make_group(runs[i], st, p.kern);
             a.g[i].block0 = blocks;
             blocks += (int64_t)a.g[i].ntiles * a.g[i].batch;
         }
@@ -436,7 +437,7 @@ static StepPlan make_plan(std::vector<GroupRun>& runs)
     p.speed.ngroups = (int32_t)runs.size();
     int64_t blocks = 0;
     for (size_t i = 0; i < runs.size(); ++i) {
-        Group g = make_group(runs[i], 0);
+        Group g = make_group(runs[i], 0, p.kern);
         g.src = runs[i].state;
         g.block0 = blocks;
         const int64_t per = (runs[i].s->cells + p.kern->cells_per_block - 1) / p.kern->cells_per_block;

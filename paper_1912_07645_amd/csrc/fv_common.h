@@ -29,6 +29,20 @@ struct Phys {
     double grav;         // shallow water: g
 };
 
+// Quotient of integers below 2^31 by a fixed divisor, as a multiplication and a shift
+// (mul = ceil(2^(31 + shift) / d), shift = ceil(log2 d)).
+struct Divisor {
+    uint32_t mul, shift;
+    __host__ __device__ uint32_t quotient(uint32_t n) const { return (uint32_t)(((uint64_t)n * mul) >> 31 >> shift); }
+};
+
+inline Divisor make_divisor(uint32_t d)
+{
+    uint32_t s = 0;
+    while (((uint64_t)1 << s) < d) ++s;
+    return Divisor{(uint32_t)((((uint64_t)1 << (31 + s)) + d - 1) / d), s};
+}
+
 // One group of samples on one grid (a batched launch covers one or more groups).
 struct Group {
     const double* src;         // U^(s-1): [batch][NF][cells]
@@ -44,6 +58,7 @@ struct Group {
     int32_t ntiles;            // tiles[0] * tiles[1] * tiles[2]
     int32_t batch;
     int64_t block0;            // first block of this group in a multi-group launch
+    Divisor by_ntiles, by_t0, by_t1;   // quotients by ntiles and by the launch's tiles along x and y
     Phys ph;
     // Split-buffer subdomains (the halo-layout kernels only): the array holds the owned cells
     // n[k] at offset off[k] inside an extent pn[k] per axis (cells = pn[0] pn[1] pn[2]); on the
@@ -55,6 +70,14 @@ struct Group {
     int32_t tlo[3];
     int32_t tcnt[3];
 };
+
+// The divisors of a launch over t[0] x t[1] x t[2] = ntiles tiles of every sample.
+inline void set_divisors(Group& g, const int32_t* t)
+{
+    g.by_ntiles = make_divisor((uint32_t)g.ntiles);
+    g.by_t0 = make_divisor((uint32_t)t[0]);
+    g.by_t1 = make_divisor((uint32_t)t[1]);
+}
 
 constexpr int kMaxGroups = 8;
 

@@ -430,6 +430,7 @@ static Group decomp_group(const fv_decomp* d, int sub, const double* src, const 
         g.tcnt[k] = cnt[k];
         g.ntiles *= cnt[k];
     }
+    set_divisors(g, g.tcnt);
     g.hmask = d->hmask;
     g.batch = d->geo.batch;
     g.ph = d->s->ph;
