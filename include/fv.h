@@ -207,8 +207,11 @@ fv_status fv_evolve_multi(int32_t n_groups, fv_solver* const* solvers, double* c
  * sample in one workgroup (state in LDS, the step decision on the chip, one launch per
  * 65 536 steps), for latency-bound small problems; its tile is the whole grid. Step
  * profiling (fv_profile_enable) and fv_evolve_multi use the tiled kernels.
+ * Until a variant is selected, by fv_set_variant or fv_tune, a solver runs variant 0, except
+ * that a large 2D batch runs the row-marching variant of its scheme, if it has one (a 64-column
+ * tile, listed like the others).
  * fv_num_variants returns their number (-1 on NULL); fv_set_variant selects one (FV_EINVAL
- * if out of range); fv_get_tile reports the current tile shape in cells and its variant
+ * if out of range); fv_get_tile reports the selected tile shape in cells and its variant
  * index (any output may be NULL). */
 int32_t fv_num_variants(const fv_solver* solver);
 fv_status fv_set_variant(fv_solver* solver, int32_t variant);

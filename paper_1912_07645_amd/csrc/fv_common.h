@@ -112,10 +112,13 @@ struct StageKernel {
     void (*speed)(const SpeedArgs&, hipStream_t);
     int32_t bx, by, bz;       // tile shape in cells
     int32_t cells_per_block;  // cells the speed kernel covers per block
+    bool march;               // a row-marching kernel (2D): one wavefront to a tile
 };
 
 // Registry (filled by the instantiation units).
 const StageKernel* find_stage_kernel(int dim, int eq, int recon, int flux, int variant);
 int num_stage_variants(int dim, int eq, int recon, int flux);
+// The row-marching kernel of a combination, if it has one.
+const StageKernel* find_march_kernel(int dim, int eq, int recon, int flux);
 
 }  // namespace fvk

@@ -29,6 +29,7 @@ FV_DECLARE_UNIT(unit_godunov)
 FV_DECLARE_UNIT(unit_ec)
 FV_DECLARE_UNIT(unit_mhd)
 FV_DECLARE_UNIT(unit_swe)
+FV_DECLARE_UNIT(unit_rows2d)
 
 }  // namespace fvk
 
@@ -40,6 +41,8 @@ FV_DECLARE_UNIT(unit_swe)
 
 #define FV_ENTRY_Z(E, R, F, X, Y, Z, NT, WPE) \
     RegEntry{3, E, R, F, make_stage_kernel_z<E, R, F, X, Y, Z, NT, WPE>()}
+
+#define FV_ENTRY_Y(E, R, F) RegEntry{2, E, R, F, make_stage_kernel_y<E, R, F>()}
 
 #define FV_ALL_RF(D, E, X, Y, Z, NT)                                                          \
     FV_ENTRY(D, E, REC_FIRST, FLUX_RUSANOV, X, Y, Z, NT), FV_ENTRY(D, E, REC_FIRST, FLUX_HLL, X, Y, Z, NT), \

@@ -609,7 +609,7 @@ template <int DIM, int EQ, int RECON, int FLUX, int BX, int BY, int BZ, int NT,
 constexpr StageKernel make_stage_kernel()
 {
     return StageKernel{&launch_stage<DIM, EQ, RECON, FLUX, BX, BY, BZ, NT, HOLD, HALO>,
-                       &launch_speed<DIM, EQ, HALO>, BX, BY, BZ, kSpeedCellsPerBlock};
+                       &launch_speed<DIM, EQ, HALO>, BX, BY, BZ, kSpeedCellsPerBlock, false};
 }
 
 }  // namespace fvk

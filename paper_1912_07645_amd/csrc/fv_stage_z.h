@@ -300,7 +300,7 @@ template <int EQ, int RECON, int FLUX, int BX, int BY, int BZ, int NT, int WPE>
 constexpr StageKernel make_stage_kernel_z()
 {
     return StageKernel{&launch_stage_z<EQ, RECON, FLUX, BX, BY, BZ, NT, WPE>, &launch_speed<3, EQ>,
-                       BX, BY, BZ, kSpeedCellsPerBlock};
+                       BX, BY, BZ, kSpeedCellsPerBlock, false};
 }
 
 }  // namespace fvk
