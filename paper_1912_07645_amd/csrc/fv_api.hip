@@ -47,7 +47,7 @@ static std::vector<RegEntry>& registry()
                                             unit_euler3d, unit_euler3d_hot, unit_scalar1d,
                                             unit_scalar2d, unit_scalar3d, unit_more1d,
                                             unit_more2d, unit_more3d, unit_swe, unit_godunov,
-                                            unit_ec, unit_mhd, unit_rows2d};
+                                            unit_ec, unit_mhd, unit_rows2d, unit_planes3d};
         for (auto u : units) {
             int n = 0;
             const RegEntry* t = u(&n);
@@ -78,9 +78,10 @@ const StageKernel* find_stage_kernel(int dim, int eq, int recon, int flux, int v
 
 const StageKernel* find_march_kernel(int dim, int eq, int recon, int flux)
 {
+    const StageKernel* k = nullptr;   // the last one: the shortest segments
     for (const RegEntry& e : registry())
-        if (e.dim == dim && e.eq == eq && e.recon == recon && e.flux == flux && e.k.march) return &e.k;
-    return nullptr;
+        if (e.dim == dim && e.eq == eq && e.recon == recon && e.flux == flux && e.k.march) k = &e.k;
+    return k;
 }
 
 }  // namespace fvk
@@ -406,24 +407,34 @@ struct StepPlan {
     const StageKernel* kern = nullptr;
 };
 
-// Whether a solver left to its default runs the row-marching kernel: with enough segments for
-// three rounds of the 4096 wavefronts that fit the chip (4 per SIMD), and strips of 64 columns
-// that are at least four fifths full on every grid. Measured, tile -> march, us per step:
-// WENO3 + HLLC 256^2 x 256 samples (16384 segments) 1592 -> 1439, 2048^2 (4096) 372 -> 395;
-// MUSCL + HLL 256^2 x 256 (32768) 836 -> 740, 256^2 x 40 (5120) 134 -> 133, 512^2 x 8 (4096)
-// 106 -> 113: with fewer segments the last round leaves much of the chip idle.
+// Whether a solver left to its default runs the marching kernel of its scheme: on enough tiles
+// to fill the chip, whose columns are at least four fifths full on every grid. us per step,
+// tile -> march.
+// By rows (2D, a wavefront to a tile; three rounds of the 4096 that fit): WENO3 + HLLC, 256^2 x
+// 256 samples (16384 tiles) 1567 -> 1412, 2048^2 (8192) 364 -> 377; MUSCL + HLL, 256^2 x 256
+// (32768) 820 -> 748, 256^2 x 40 (5120) 133 -> 132, 512^2 x 8 (4096) 106 -> 113. Fewer tiles
+// leave much of the chip idle in the last round.
+// By planes (3D, a workgroup to a tile; 768 fit): WENO3 + HLLC, 64^3 x 8 (640 tiles) 506 -> 474,
+// 128^3 (576) 496 -> 494, 96^3 (252) 235 -> 271, 256^3 (4608) 3322 -> 2527; MUSCL + HLL, 64^3 x 8
+// 285 -> 251, 96^3 128 -> 150, 256^3 2094 -> 1263; 17 x 200 x 200 x 4, its columns half empty,
+// 629 -> 892.
 static bool march_pays(const std::vector<GroupRun>& runs)
 {
     const fv_solver* s0 = runs[0].s;
-    if (!s0->march || s0->variant_set) return false;
-    int64_t segments = 0;
+    const StageKernel* k = s0->march;
+    if (!k || s0->variant_set) return false;
+    int64_t tiles = 0;
     for (const GroupRun& r : runs) {
-        const int64_t nx = r.s->grid.n[0], ny = r.s->grid.n[1];
-        const int64_t strips = (nx + s0->march->bx - 1) / s0->march->bx;
-        if (5 * nx < 4 * strips * s0->march->bx) return false;
-        segments += strips * ((ny + s0->march->by - 1) / s0->march->by) * r.batch;
+        const int64_t* n = r.s->grid.n;
+        int64_t t[3];
+        const int32_t b[3] = {k->bx, k->by, k->bz};
+        for (int i = 0; i < 3; ++i) t[i] = (n[i] + b[i] - 1) / b[i];
+        const int64_t across = k->march == kMarchRows ? 1 : n[1];          // columns in use, and
+        const int64_t room = k->march == kMarchRows ? t[0] * b[0] : t[0] * b[0] * t[1] * b[1];
+        if (5 * n[0] * across < 4 * room) return false;                      // columns there are
+        tiles += t[0] * t[1] * t[2] * r.batch;
     }
-    return segments >= 3 * 4096;
+    return tiles >= (k->march == kMarchRows ? 3 * 4096 : 640);
 }
 
 static StepPlan make_plan(std::vector<GroupRun>& runs)
@@ -431,6 +442,12 @@ static StepPlan make_plan(std::vector<GroupRun>& runs)
     StepPlan p;
     const fv_solver* s0 = runs[0].s;
     p.kern = march_pays(runs) ? s0->march : s0->kern;
+    if (p.kern->march == kMarchPlanes) {
+        // planes beyond the kernel's 32-bit offsets: the scheme's first tile (same results)
+        for (const GroupRun& r : runs)
+            if (r.s->grid.n[0] * r.s->grid.n[1] >= kMaxPlane)
+                p.kern = find_stage_kernel(s0->grid.dim, s0->eq.kind, s0->recon, s0->flux, 0);
+    }
     const int S = n_stages(s0->integ);
     for (int st = 0; st < S; ++st) {
         StageArgs a{};

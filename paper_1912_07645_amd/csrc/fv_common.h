@@ -106,13 +106,18 @@ struct SpeedArgs {
     int64_t nblocks;
 };
 
+// Marching kernels: 2D by rows (one wavefront to a tile), 3D by planes (of fewer than
+// kMaxPlane cells).
+enum { kMarchRows = 1, kMarchPlanes = 2 };
+constexpr int64_t kMaxPlane = (int64_t)1 << 29;
+
 // Host-side launchers for one (dim, equation, reconstruction, flux, tile) combination.
 struct StageKernel {
     void (*stage)(const StageArgs&, hipStream_t);
     void (*speed)(const SpeedArgs&, hipStream_t);
     int32_t bx, by, bz;       // tile shape in cells
     int32_t cells_per_block;  // cells the speed kernel covers per block
-    bool march;               // a row-marching kernel (2D): one wavefront to a tile
+    int32_t march;            // kMarchRows, kMarchPlanes or 0 (a tile at a time)
 };
 
 // Registry (filled by the instantiation units).

@@ -178,69 +178,118 @@ __device__ __forceinline__ double minmod_finite(double a, double b)
     return fmax1(fmin1(a, b), 0.0) + fmin1(fmax1(a, b), 0.0);
 }
 
-// Numerators and denominators of weno3(a, b, c) (left) and weno3(d, c, b) (right), both halved
-// where the written form has the factor two:
-// 2 t1 (b + c)/2 + t0 (3b - a)/2 = t1 (b + c) + (t0/2)(3b - a).
-__device__ __forceinline__ void weno3_terms(double a, double b, double c, double d, double& nL,
-                                            double& dL, double& nR, double& dR)
+// Numerators and denominators of weno3(a, b, c) and weno3(d, c, b) from the smoothness terms
+// t = ((difference)^2 + eps)^2 of (a, b), (b, c) and (c, d).
+__device__ __forceinline__ void weno3_terms(double a, double b, double c, double d, double tab,
+                                            double tbc, double tcd, double* n, double* den)
 {
-    const double dbc = c - b, dab = b - a, ddc = c - d;
-    double tbc = __builtin_fma(dbc, dbc, 1e-6);
-    tbc = tbc * tbc;
-    double tab = __builtin_fma(dab, dab, 1e-6);
-    tab = tab * tab;
-    double tdc = __builtin_fma(ddc, ddc, 1e-6);
-    tdc = tdc * tdc;
+    // 2 t1 (b + c)/2 + t0 (3b - a)/2 = t1 (b + c) + (t0/2)(3b - a)
     const double s = b + c, h = 0.5 * tbc;
-    nL = __builtin_fma(tab, s, h * __builtin_fma(3.0, b, -a));
-    nR = __builtin_fma(tdc, s, h * __builtin_fma(3.0, c, -d));
-    dL = __builtin_fma(2.0, tab, tbc);
-    dR = __builtin_fma(2.0, tdc, tbc);
+    n[0] = __builtin_fma(tab, s, h * __builtin_fma(3.0, b, -a));
+    n[1] = __builtin_fma(tcd, s, h * __builtin_fma(3.0, c, -d));
+    den[0] = __builtin_fma(2.0, tab, tbc);
+    den[1] = __builtin_fma(2.0, tcd, tbc);
+}
+
+// Smoothness term of two neighbouring cells (the sign of the difference does not matter).
+__device__ __forceinline__ double weno3_smooth(double a, double b)
+{
+    const double d = b - a;
+    const double t = __builtin_fma(d, d, 1e-6);
+    return t * t;
+}
+
+// WENO3 states of every field at a face; terms(q, n, den) gives a field's two numerators and
+// denominators. Two fields at a time: four denominators share a reciprocal.
+template <int NF, class Terms>
+__device__ __forceinline__ void weno3_states(const Terms& terms, double* UL, double* UR)
+{
+#pragma unroll
+    for (int q = 0; q + 1 < NF; q += 2) {
+        double n[4], d[4], y[4];
+        terms(q, n, d);
+        terms(q + 1, n + 2, d + 2);
+        recips(d, y);
+        UL[q] = quotient(n[0], d[0], y[0]);
+        UR[q] = quotient(n[1], d[1], y[1]);
+        UL[q + 1] = quotient(n[2], d[2], y[2]);
+        UR[q + 1] = quotient(n[3], d[3], y[3]);
+    }
+    if constexpr (NF % 2) {
+        constexpr int q = NF - 1;
+        double n[2], d[2], y[2];
+        terms(q, n, d);
+        recips(d, y);
+        UL[q] = quotient(n[0], d[0], y[0]);
+        UR[q] = quotient(n[1], d[1], y[1]);
+    }
 }
 
 // Left and right states of every field at a face from at(q, j), field q of cell i - 2 + j.
-// WENO3 takes the fields two at a time: four denominators share a reciprocal.
-template <int RECON, int NF, class Cells>
-__device__ __forceinline__ void reconstruct_tame(const Cells& at, double* UL, double* UR)
-{
-    if constexpr (RECON == REC_FIRST) {
+struct Reconstruct {
+    template <int RECON, int NF, class Cells>
+    __device__ __forceinline__ void states(const Cells& at, double* UL, double* UR)
+    {
+        if constexpr (RECON == REC_FIRST) {
 #pragma unroll
-        for (int q = 0; q < NF; ++q) {
-            UL[q] = at(q, 1);
-            UR[q] = at(q, 2);
-        }
-    } else if constexpr (RECON == REC_MUSCL) {
+            for (int q = 0; q < NF; ++q) {
+                UL[q] = at(q, 1);
+                UR[q] = at(q, 2);
+            }
+        } else if constexpr (RECON == REC_MUSCL) {
 #pragma unroll
-        for (int q = 0; q < NF; ++q) {
-            const double b = at(q, 1), c = at(q, 2), m = c - b;
-            UL[q] = __builtin_fma(0.5, minmod_finite(b - at(q, 0), m), b);
-            UR[q] = __builtin_fma(-0.5, minmod_finite(m, at(q, 3) - c), c);
-        }
-    } else if constexpr (RECON == REC_ENO2) {
+            for (int q = 0; q < NF; ++q) {
+                const double b = at(q, 1), c = at(q, 2), m = c - b;
+                UL[q] = __builtin_fma(0.5, minmod_finite(b - at(q, 0), m), b);
+                UR[q] = __builtin_fma(-0.5, minmod_finite(m, at(q, 3) - c), c);
+            }
+        } else if constexpr (RECON == REC_ENO2) {
 #pragma unroll
-        for (int q = 0; q < NF; ++q) reconstruct<REC_ENO2>(at(q, 0), at(q, 1), at(q, 2), at(q, 3), UL[q], UR[q]);
-    } else {
-#pragma unroll
-        for (int q = 0; q + 1 < NF; q += 2) {
-            double n[4], d[4], y[4];
-            weno3_terms(at(q, 0), at(q, 1), at(q, 2), at(q, 3), n[0], d[0], n[1], d[1]);
-            weno3_terms(at(q + 1, 0), at(q + 1, 1), at(q + 1, 2), at(q + 1, 3), n[2], d[2], n[3], d[3]);
-            recips(d, y);
-            UL[q] = quotient(n[0], d[0], y[0]);
-            UR[q] = quotient(n[1], d[1], y[1]);
-            UL[q + 1] = quotient(n[2], d[2], y[2]);
-            UR[q + 1] = quotient(n[3], d[3], y[3]);
-        }
-        if constexpr (NF % 2) {
-            constexpr int q = NF - 1;
-            double n[2], d[2], y[2];
-            weno3_terms(at(q, 0), at(q, 1), at(q, 2), at(q, 3), n[0], d[0], n[1], d[1]);
-            recips(d, y);
-            UL[q] = quotient(n[0], d[0], y[0]);
-            UR[q] = quotient(n[1], d[1], y[1]);
+            for (int q = 0; q < NF; ++q)
+                reconstruct<REC_ENO2>(at(q, 0), at(q, 1), at(q, 2), at(q, 3), UL[q], UR[q]);
+        } else {
+            weno3_states<NF>([&](int q, double* n, double* d) {
+                const double a = at(q, 0), b = at(q, 1), c = at(q, 2), e = at(q, 3);
+                weno3_terms(a, b, c, e, weno3_smooth(a, b), weno3_smooth(b, c), weno3_smooth(e, c), n, d);
+            }, UL, UR);
         }
     }
-}
+};
+
+// The same for the faces of a march along one axis, each a cell further than the one before:
+// WENO3 keeps the smoothness terms of the last two pairs of cells, and forms one of three anew.
+template <int RECON, int NF>
+struct MarchReconstruct {
+    static constexpr bool KEEP = RECON == REC_WENO3;
+    double ta[KEEP ? NF : 1], tb[KEEP ? NF : 1];   // of cells 0 and 1, 1 and 2 of the next face
+
+    template <class Cells>
+    __device__ __forceinline__ void start(const Cells& at)
+    {
+        if constexpr (KEEP) {
+#pragma unroll
+            for (int q = 0; q < NF; ++q) {
+                ta[q] = weno3_smooth(at(q, 0), at(q, 1));
+                tb[q] = weno3_smooth(at(q, 1), at(q, 2));
+            }
+        }
+    }
+    template <int, int, class Cells>
+    __device__ __forceinline__ void states(const Cells& at, double* UL, double* UR)
+    {
+        if constexpr (KEEP) {
+            weno3_states<NF>([&](int q, double* n, double* d) {
+                const double a = at(q, 0), b = at(q, 1), c = at(q, 2), e = at(q, 3);
+                const double tc = weno3_smooth(e, c);
+                weno3_terms(a, b, c, e, ta[q], tb[q], tc, n, d);
+                ta[q] = tb[q];
+                tb[q] = tc;
+            }, UL, UR);
+        } else {
+            Reconstruct().states<RECON, NF>(at, UL, UR);
+        }
+    }
+};
 
 // ---------------------------------------------------------------- Euler
 
@@ -407,40 +456,75 @@ constexpr bool cells_need_finite()
            !(EQ == EQ_EULER && (FLUX == FLUX_RUSANOV || FLUX == FLUX_HLL || FLUX == FLUX_HLLC));
 }
 
-// The cells around a face in LDS: field q of cell i - 2 + j at s[q * QS + (j - 2) * STRIDE].
+// Cells around a face. reread() gives the same values to the general path in a form that keeps the
+// compiler from holding what the short path computed from them (differences, smoothness terms)
+// until then: that took 50 registers of the 3D marching kernel.
+// In LDS: field q of cell i - 2 + j at s[q * QS + (j - 2) * STRIDE].
 template <int QS, int STRIDE>
 struct LdsCells {
     const double* su;
     int c;
     __device__ __forceinline__ double operator()(int q, int j) const { return su[q * QS + c + (j - 2) * STRIDE]; }
-    // read again from here on: values loaded before are not kept in registers for later
-    __device__ __forceinline__ void reload() { asm volatile("" : "+v"(c)); }
+    __device__ __forceinline__ LdsCells reread() const
+    {
+        LdsCells r{su, c};
+        asm volatile("" : "+v"(r.c));
+        return r;
+    }
+};
+
+// The same for cells in registers: each value as if new.
+template <class Cells>
+struct Reread {
+    const Cells& at;
+    __device__ __forceinline__ double operator()(int q, int j) const
+    {
+        double v = at(q, j);
+        asm volatile("" : "+v"(v));
+        return v;
+    }
+};
+
+// Cells of a face in registers: cell i - 2 + j at w[j - 2 + G].
+template <int NF, int G>
+struct RowCells {
+    const double (&w)[2 * G][NF];
+    __device__ __forceinline__ double operator()(int q, int j) const { return w[j - 2 + G][q]; }
+    __device__ __forceinline__ Reread<RowCells> reread() const { return Reread<RowCells>{*this}; }
 };
 
 // Flux at the face with normal axis ND between cells i - 1 and i; at(q, j): field q of cell
-// i - 2 + j (j = 1, 2 only for first order). tame: uniform over the wavefront.
-template <int DIM, int EQ, int RECON, int FLUX, int ND, class Cells>
-__device__ __forceinline__ void face_flux(Cells at, const Phys& ph, bool tame, double* F)
+// i - 2 + j (j = 1, 2 only for first order). tame: uniform over the wavefront. rec: how the short
+// path reconstructs (once not tame, a march stays so: its kept terms are not used again).
+template <int DIM, int EQ, int RECON, int FLUX, int ND, class Cells, class Rec>
+__device__ __forceinline__ void face_flux(const Cells& at, const Phys& ph, bool tame, double* F, Rec& rec)
 {
     constexpr int NF = NumFields<DIM, EQ>::value;
     if constexpr (has_tame_face<EQ, RECON, FLUX>()) {
         if (tame) {
             double UL[NF], UR[NF];
-            reconstruct_tame<RECON, NF>(at, UL, UR);
+            rec.template states<RECON, NF>(at, UL, UR);
             const bool ok = numflux_tame<DIM, EQ, FLUX>(UL, UR, ND, F, ph);
             if (!any_lane(!ok)) return;
         }
-        at.reload();
     }
     double UL[NF], UR[NF];
+    const auto cell = at.reread();
 #pragma unroll
     for (int q = 0; q < NF; ++q) {
         if constexpr (RECON == REC_FIRST)
-            reconstruct<RECON>(0.0, at(q, 1), at(q, 2), 0.0, UL[q], UR[q]);
+            reconstruct<RECON>(0.0, cell(q, 1), cell(q, 2), 0.0, UL[q], UR[q]);
         else
-            reconstruct<RECON>(at(q, 0), at(q, 1), at(q, 2), at(q, 3), UL[q], UR[q]);
+            reconstruct<RECON>(cell(q, 0), cell(q, 1), cell(q, 2), cell(q, 3), UL[q], UR[q]);
     }
     numflux<DIM, EQ, FLUX>(UL, UR, ND, F, ph);
+}
+
+template <int DIM, int EQ, int RECON, int FLUX, int ND, class Cells>
+__device__ __forceinline__ void face_flux(const Cells& at, const Phys& ph, bool tame, double* F)
+{
+    Reconstruct rec;
+    face_flux<DIM, EQ, RECON, FLUX, ND>(at, ph, tame, F, rec);
 }
 
 }  // namespace fvk

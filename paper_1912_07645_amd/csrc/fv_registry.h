@@ -30,6 +30,7 @@ FV_DECLARE_UNIT(unit_ec)
 FV_DECLARE_UNIT(unit_mhd)
 FV_DECLARE_UNIT(unit_swe)
 FV_DECLARE_UNIT(unit_rows2d)
+FV_DECLARE_UNIT(unit_planes3d)
 
 }  // namespace fvk
 
@@ -39,8 +40,8 @@ FV_DECLARE_UNIT(unit_rows2d)
 #define FV_ENTRY_H(D, E, R, F, X, Y, Z, NT, H) \
     RegEntry{D, E, R, F, make_stage_kernel<D, E, R, F, X, Y, Z, NT, H>()}
 
-#define FV_ENTRY_Z(E, R, F, X, Y, Z, NT, WPE) \
-    RegEntry{3, E, R, F, make_stage_kernel_z<E, R, F, X, Y, Z, NT, WPE>()}
+#define FV_ENTRY_Z(E, R, F, X, Y, Z, NT) \
+    RegEntry{3, E, R, F, make_stage_kernel_z<E, R, F, X, Y, Z, NT>()}
 
 #define FV_ENTRY_Y(E, R, F) RegEntry{2, E, R, F, make_stage_kernel_y<E, R, F>()}
 

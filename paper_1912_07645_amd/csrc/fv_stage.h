@@ -78,6 +78,16 @@ __device__ __forceinline__ T* at_byte(T* p, uint32_t off)
     return (T*)((Byte*)p + off);
 }
 
+// Where row (or plane) `row` of n cells starts, its offset kept in scalar registers (left to
+// itself the compiler makes a march's addresses per-lane pointers, a pair of registers each).
+template <class T>
+__device__ __forceinline__ T* row_ptr(T* base, int32_t row, int32_t n)
+{
+    int64_t o = (int64_t)row * n;
+    asm volatile("" : "+s"(o));
+    return base + o;
+}
+
 template <int DIM, int EQ, int RECON, int BX, int BY, int BZ, int NT>
 struct StageTile {
     static constexpr int NF = NumFields<DIM, EQ>::value;
@@ -609,7 +619,7 @@ template <int DIM, int EQ, int RECON, int FLUX, int BX, int BY, int BZ, int NT,
 constexpr StageKernel make_stage_kernel()
 {
     return StageKernel{&launch_stage<DIM, EQ, RECON, FLUX, BX, BY, BZ, NT, HOLD, HALO>,
-                       &launch_speed<DIM, EQ, HALO>, BX, BY, BZ, kSpeedCellsPerBlock, false};
+                       &launch_speed<DIM, EQ, HALO>, BX, BY, BZ, kSpeedCellsPerBlock, 0};
 }
 
 }  // namespace fvk

@@ -46,14 +46,6 @@ struct Strip {
     static_assert(R <= kStrip, "one lane per row before the march");
 };
 
-// Cells of a face held in an array: column j of w.
-template <int NF, int G>
-struct RowCells {
-    const double (&w)[2 * G][NF];
-    __device__ __forceinline__ double operator()(int q, int j) const { return w[j - 2 + G][q]; }
-    __device__ __forceinline__ void reload() {}
-};
-
 // Cells around the x face on the left of a lane's own cell (from registers), the others from
 // the row in LDS; s is the lane's.
 template <int NF, int G, int QS>
@@ -65,18 +57,8 @@ struct StripCells {
     {
         return j == 2 ? own[q] : row[q * QS + lane + (j - 2 + G)];
     }
-    __device__ __forceinline__ void reload() { asm volatile("" : "+v"(lane)); }
+    __device__ __forceinline__ Reread<StripCells> reread() const { return Reread<StripCells>{*this}; }
 };
-
-// First cell of a row, kept in scalar registers (left to itself the compiler turns the march's
-// addresses into per-lane 64-bit pointers, a pair of registers for every array).
-template <class T>
-__device__ __forceinline__ T* row_ptr(T* base, int32_t row, int32_t nx)
-{
-    T* p = base + (int64_t)row * nx;
-    asm volatile("" : "+s"(p));
-    return p;
-}
 
 // Orders LDS accesses of the wavefront's lanes: what was written before is read after.
 __device__ __forceinline__ void wave_fence()
@@ -183,9 +165,11 @@ stage_kernel_y(const StageArgs args)
             for (int q = 0; q < NF; ++q) range.add<FIN>(w[j][q]);
         tame = tame && !any_lane(!range.tame());
     }
+    MarchReconstruct<RECON, NF> rec;
+    rec.start(RowCells<NF, G>{w});
     {
         double F[NF];
-        face_flux<2, EQ, RECON, FLUX, 1>(RowCells<NF, G>{w}, g.ph, tame, F);
+        face_flux<2, EQ, RECON, FLUX, 1>(RowCells<NF, G>{w}, g.ph, tame, F, rec);
 #pragma unroll
         for (int q = 0; q < NF; ++q) s[q * QS + T::FY + lane] = F[q];
     }
@@ -234,7 +218,7 @@ stage_kernel_y(const StageArgs args)
             tame = tame && !any_lane(!range.tame());
         }
         double fyp[NF];
-        face_flux<2, EQ, RECON, FLUX, 1>(RowCells<NF, G>{w}, g.ph, tame, fyp);
+        face_flux<2, EQ, RECON, FLUX, 1>(RowCells<NF, G>{w}, g.ph, tame, fyp, rec);
         wave_fence();
         double unr[NF];
         if (args.use_un) {
@@ -299,7 +283,7 @@ constexpr StageKernel make_stage_kernel_y()
 {
     constexpr int R = (RECON == REC_WENO3) ? 16 : 8;
     return StageKernel{&launch_stage_y<EQ, RECON, FLUX, R, WPE>, &launch_speed<2, EQ>,
-                       kStrip, R, 1, kSpeedCellsPerBlock, true};
+                       kStrip, R, 1, kSpeedCellsPerBlock, kMarchRows};
 }
 
 }  // namespace fvk

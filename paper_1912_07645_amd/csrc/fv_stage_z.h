@@ -78,24 +78,19 @@ __device__ __forceinline__ void z_plane_face(const double* sp, const Phys& ph, b
 }
 
 // The z face above the window's middle: w[0..2G-1] are the column's cells k-G+1 .. k+G.
-template <int NF, int G>
-struct WindowCells {
-    const double (&w)[2 * G][NF];
-    __device__ __forceinline__ double operator()(int q, int j) const { return w[j - 2 + G][q]; }
-    __device__ __forceinline__ void reload() {}
-};
-
 template <int EQ, int RECON, int FLUX, int NF, int G>
-__device__ __forceinline__ void z_column_face(const double (&w)[2 * G][NF], const Phys& ph, bool tame, double* F)
+__device__ __forceinline__ void z_column_face(const double (&w)[2 * G][NF], const Phys& ph, bool tame,
+                                              double* F, MarchReconstruct<RECON, NF>& rec)
 {
-    face_flux<3, EQ, RECON, FLUX, 2>(WindowCells<NF, G>{w}, ph, tame, F);
+    face_flux<3, EQ, RECON, FLUX, 2>(RowCells<NF, G>{w}, ph, tame, F, rec);
 }
 
-// WPE: the fewest wavefronts per SIMD to compile for. The column registers make this kernel
-// need about 150 VGPRs (3 wavefronts per SIMD); at 4 some of them spill to scratch, and
-// which costs less is measured. At 3, U^n is also requested a plane ahead.
-template <int EQ, int RECON, int FLUX, int BX, int BY, int BZ, int NT, int WPE>
-__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, 8)))
+// Compiled for 3 wavefronts per SIMD, 168 registers, which it needs without a spill: with 25 of
+// them in scratch (the short and the general face path sharing subexpressions) a step of
+// 480 x 480 x 256 took 10.6 ms, without 8.2 (9.0 before the short path), since a reload waits for
+// every load issued before it. The z fluxes below a plane are kept in LDS for the same reason.
+template <int EQ, int RECON, int FLUX, int BX, int BY, int BZ, int NT>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3, 8)))
 stage_kernel_z(const StageArgs args)
 {
     using T = ZTile<EQ, RECON, BX, BY, NT>;
@@ -103,6 +98,7 @@ stage_kernel_z(const StageArgs args)
     constexpr int NFX = T::NFX, NFXY = T::NFXY;
     __shared__ double sp[NF * PP];     // current plane with its x and y halo
     __shared__ double sf[NF * NFXY];   // x faces, then y faces, of the current plane
+    __shared__ double sz[NF * NT];     // z fluxes on the lower faces of the plane's cells
     __shared__ int wild;               // a cell that is not tame was staged
     constexpr bool TAME = has_tame_face<EQ, RECON, FLUX>();
     constexpr bool FIN = cells_need_finite<EQ, RECON, FLUX>();
@@ -134,29 +130,26 @@ stage_kernel_z(const StageArgs args)
     const int col = (t < COLS) ? t : COLS - 1;
     const int cx = col % BX, cy = col / BX;
     const bool own = (t < COLS) && (x0 + cx < nx) && (y0 + cy < ny);
-    const int32_t ccol = wrap_index(y0 + cy, ny, args.bc[1]) * nx + wrap_index(x0 + cx, nx, args.bc[0]);
+    // byte offsets in a plane (a plane of this kernel has fewer than 2^29 cells): planes are
+    // addressed from scalar registers, one offset register serving every field
+    const uint32_t ccol = (uint32_t)sizeof(double) *
+        (uint32_t)(wrap_index(y0 + cy, ny, args.bc[1]) * nx + wrap_index(x0 + cx, nx, args.bc[0]));
     const int lcore = (cy + G) * PX + (cx + G);
 
     // this thread's halo cell (threads t >= NH have none)
     int hpx = 0, hpy = 0;
     if (t < NH) z_halo_pos<G, BX, BY>(t, hpx, hpy);
     const int lhalo = hpy * PX + hpx;
-    const int32_t chalo = wrap_index(y0 + hpy - G, ny, args.bc[1]) * nx
-                        + wrap_index(x0 + hpx - G, nx, args.bc[0]);
+    const uint32_t chalo = (uint32_t)sizeof(double) *
+        (uint32_t)(wrap_index(y0 + hpy - G, ny, args.bc[1]) * nx + wrap_index(x0 + hpx - G, nx, args.bc[0]));
 
     // column window: w[j] = cell z = k - G + 1 + j at the face above plane k
     double w[2 * G][NF];
 #pragma unroll
     for (int j = 0; j < 2 * G; ++j) {
-        const int32_t zc = wrap_index(z0 - G + j, nz, args.bc[2]) * plane + ccol;
+        const double* p = row_ptr(src, wrap_index(z0 - G + j, nz, args.bc[2]), plane);
 #pragma unroll
-        for (int q = 0; q < NF; ++q) w[j][q] = src[q * cells + zc];
-    }
-    double hreg[NF];
-    if (t < NH) {
-        const int32_t hc = z0 * plane + chalo;
-#pragma unroll
-        for (int q = 0; q < NF; ++q) hreg[q] = src[q * cells + hc];
+        for (int q = 0; q < NF; ++q) w[j][q] = *at_byte(p + q * cells, ccol);
     }
     CellRange range;   // of the cells this thread has loaded
     if constexpr (TAME) {
@@ -167,8 +160,34 @@ stage_kernel_z(const StageArgs args)
             for (int q = 0; q < NF; ++q) range.add<FIN>(w[j][q]);
         __syncthreads();
     }
-    double fzm[NF];   // z flux on the lower face of the current plane
-    z_column_face<EQ, RECON, FLUX, NF, G>(w, g.ph, TAME && !any_lane(!range.tame()), fzm);
+    MarchReconstruct<RECON, NF> rec;
+    rec.start(RowCells<NF, G>{w});
+    {   // z flux on the lower face of the current plane: its own LDS slot, not registers
+        double F[NF];
+        z_column_face<EQ, RECON, FLUX, NF, G>(w, g.ph, TAME && !any_lane(!range.tame()), F, rec);
+#pragma unroll
+        for (int q = 0; q < NF; ++q) sz[q * NT + t] = F[q];
+    }
+    // stage the halo of a plane, loaded before, and look at its cells
+    auto stage_halo = [&](const double (&h)[NF]) {
+        if (t < NH) {
+#pragma unroll
+            for (int q = 0; q < NF; ++q) sp[q * PP + lhalo] = h[q];
+            if constexpr (TAME) {
+#pragma unroll
+                for (int q = 0; q < NF; ++q) range.add<FIN>(h[q]);
+            }
+        }
+    };
+    {
+        double h[NF];
+        if (t < NH) {
+            const double* p = row_ptr(src, z0, plane);
+#pragma unroll
+            for (int q = 0; q < NF; ++q) h[q] = *at_byte(p + q * cells, chalo);
+        }
+        stage_halo(h);
+    }
 #pragma unroll
     for (int j = 0; j + 1 < 2 * G; ++j)
 #pragma unroll
@@ -180,46 +199,31 @@ stage_kernel_z(const StageArgs args)
     bool bad = false;
 
     for (int32_t k = z0; k < z1; ++k) {
-        // 1. stage plane k: its own cells from the column registers, the halo from registers
-        //    filled one plane ahead
+        // 1. stage plane k: its own cells from the column registers (its halo is there already)
         if (t < COLS) {
 #pragma unroll
             for (int q = 0; q < NF; ++q) sp[q * PP + lcore] = w[G - 1][q];
         }
-        if (t < NH) {
-#pragma unroll
-            for (int q = 0; q < NF; ++q) sp[q * PP + lhalo] = hreg[q];
-            if constexpr (TAME) {
-#pragma unroll
-                for (int q = 0; q < NF; ++q) range.add<FIN>(hreg[q]);
-            }
-        }
         if constexpr (TAME) {
             if (!range.tame()) wild = 1;
         }
-        // 2. request the column cell k + G, the halo of plane k + 1 and (compiled for 3
-        //    wavefronts per SIMD, where the registers are there) U^n of the updated cell
+        // 2. request the column cell k + G and the halo of plane k + 1
         {
-            const int32_t zc = wrap_index(k + G, nz, args.bc[2]) * plane + ccol;
+            const double* p = row_ptr(src, wrap_index(k + G, nz, args.bc[2]), plane);
 #pragma unroll
-            for (int q = 0; q < NF; ++q) w[2 * G - 1][q] = src[q * cells + zc];
+            for (int q = 0; q < NF; ++q) w[2 * G - 1][q] = *at_byte(p + q * cells, ccol);
         }
+        double hreg[NF];
         if (t < NH && k + 1 < z1) {
-            const int32_t hc = (k + 1) * plane + chalo;
+            const double* p = row_ptr(src, k + 1, plane);
 #pragma unroll
-            for (int q = 0; q < NF; ++q) hreg[q] = src[q * cells + hc];
-        }
-        double unr[NF];
-        if (WPE <= 3 && args.use_un) {
-            const int32_t cc = k * plane + ccol;
-#pragma unroll
-            for (int q = 0; q < NF; ++q) unr[q] = un[q * cells + cc];
+            for (int q = 0; q < NF; ++q) hreg[q] = *at_byte(p + q * cells, chalo);
         }
         __syncthreads();
         const bool tame = TAME && __builtin_amdgcn_readfirstlane(wild) == 0;
 
         // 3. x and y faces of the plane (each axis padded to whole wavefronts)
-#pragma unroll
+#pragma unroll 1
         for (int p = 0; p < T::FPT; ++p) {
             const int pf = t + p * NT;
             if (pf < T::TOTAL) {
@@ -242,32 +246,38 @@ stage_kernel_z(const StageArgs args)
                 }
             }
         }
-        // 4. the z face above plane k, in registers
+        // 4. U^n of the updated cell requested; the z face above plane k, in registers
+        double unr[NF];
+        if (args.use_un) {
+            const double* p = row_ptr(un, k, plane);
+#pragma unroll
+            for (int q = 0; q < NF; ++q) unr[q] = *at_byte(p + q * cells, ccol);
+        }
         double fzp[NF];
         if constexpr (TAME) {
 #pragma unroll
             for (int q = 0; q < NF; ++q) range.add<FIN>(w[2 * G - 1][q]);
         }
-        z_column_face<EQ, RECON, FLUX, NF, G>(w, g.ph, TAME && !any_lane(!range.tame()), fzp);
+        z_column_face<EQ, RECON, FLUX, NF, G>(w, g.ph, TAME && !any_lane(!range.tame()), fzp, rec);
         __syncthreads();
 
         // 5. divergence (x, y, z) and the Runge--Kutta stage combination
         if (own) {
             const int fxm = cy * (BX + 1) + cx;
             const int fym = NFX + cy * BX + cx;
-            const int32_t gidx = k * plane + ccol;
+            double* pd = row_ptr(dst, k, plane);
             double out[NF];
 #pragma unroll
             for (int q = 0; q < NF; ++q) {
                 const double* F = sf + q * NFXY;
                 double acc = (F[fxm + 1] - F[fxm]) * g.ph.inv_dx[0];
                 acc = acc + ((F[fym + BX] - F[fym]) * g.ph.inv_dx[1]);
-                acc = acc + ((fzp[q] - fzm[q]) * g.ph.inv_dx[2]);
+                acc = acc + ((fzp[q] - sz[q * NT + t]) * g.ph.inv_dx[2]);
                 const double rhs = -acc;
                 const double up = w[G - 1][q];
-                const double u0q = args.use_un ? (WPE <= 3 ? unr[q] : un[q * cells + gidx]) : up;
+                const double u0q = args.use_un ? unr[q] : up;
                 out[q] = u0q + (beta * ((up - u0q) + (dt * rhs)));
-                dst[q * cells + gidx] = out[q];
+                *at_byte(pd + q * cells, ccol) = out[q];
             }
             if (args.last) {
                 bool b;
@@ -276,9 +286,11 @@ stage_kernel_z(const StageArgs args)
                 bad = bad || b;
             }
         }
-        // 6. slide the column window up by one plane
+        // 6. the next plane's halo (after the barrier above no face reads this one's); slide the
+        //    column window up by one plane
+        if (k + 1 < z1) stage_halo(hreg);
 #pragma unroll
-        for (int q = 0; q < NF; ++q) fzm[q] = fzp[q];
+        for (int q = 0; q < NF; ++q) sz[q * NT + t] = fzp[q];
 #pragma unroll
         for (int j = 0; j + 1 < 2 * G; ++j)
 #pragma unroll
@@ -289,18 +301,18 @@ stage_kernel_z(const StageArgs args)
                               &g.bad[sample]);
 }
 
-template <int EQ, int RECON, int FLUX, int BX, int BY, int BZ, int NT, int WPE>
+template <int EQ, int RECON, int FLUX, int BX, int BY, int BZ, int NT>
 void launch_stage_z(const StageArgs& a, hipStream_t s)
 {
-    hipLaunchKernelGGL((stage_kernel_z<EQ, RECON, FLUX, BX, BY, BZ, NT, WPE>),
+    hipLaunchKernelGGL((stage_kernel_z<EQ, RECON, FLUX, BX, BY, BZ, NT>),
                        dim3((unsigned)a.nblocks), dim3(NT), 0, s, a);
 }
 
-template <int EQ, int RECON, int FLUX, int BX, int BY, int BZ, int NT, int WPE>
+template <int EQ, int RECON, int FLUX, int BX, int BY, int BZ, int NT>
 constexpr StageKernel make_stage_kernel_z()
 {
-    return StageKernel{&launch_stage_z<EQ, RECON, FLUX, BX, BY, BZ, NT, WPE>, &launch_speed<3, EQ>,
-                       BX, BY, BZ, kSpeedCellsPerBlock, false};
+    return StageKernel{&launch_stage_z<EQ, RECON, FLUX, BX, BY, BZ, NT>, &launch_speed<3, EQ>,
+                       BX, BY, BZ, kSpeedCellsPerBlock, kMarchPlanes};
 }
 
 }  // namespace fvk
