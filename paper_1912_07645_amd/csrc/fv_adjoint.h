@@ -22,6 +22,7 @@ struct AdjArgs {
     int32_t n[3];
     int32_t tiles[3];
     int32_t ntiles;
+    Divisor by_ntiles, by_t0;   // quotients by ntiles and tiles[0]
     int32_t batch;
     int32_t bc[3];
     int32_t mode;

@@ -47,27 +47,85 @@ __device__ __forceinline__ void euler_flux_jt(const double* U, const EulerPrim<D
     out[NF - 1] = wE * un + Wp * p_E;
 }
 
-// Gradient of |u_n| + c with respect to U.
+// One side of a face, as speed_grad needs it.
 template <int DIM>
-__device__ __forceinline__ void speed_grad(const double* U, const EulerPrim<DIM>& pr, int nd,
-                                           const Phys& ph, double* g)
+struct SpeedSide {
+    double rho, ir, c, u[DIM];
+};
+
+// Gradient of |u_n| + c with respect to U; TAME: the quotients of fv_fast.h.
+template <int DIM, bool TAME>
+__device__ __forceinline__ void speed_grad(const SpeedSide<DIM>& k, int nd, const Phys& ph, double* g)
 {
     constexpr int NF = DIM + 2;
-    const double un = pick<DIM>(pr.u, nd);
+    const double un = pick<DIM>(k.u, nd);
     const double sg = (un > 0.0) ? 1.0 : ((un < 0.0) ? -1.0 : 0.0);
     double usq = 0.0;
 #pragma unroll
-    for (int k = 0; k < DIM; ++k) usq = usq + pr.u[k] * pr.u[k];
-    const double a = ph.gamma / (2.0 * pr.c * U[0]);       // dc/dp
+    for (int j = 0; j < DIM; ++j) usq = usq + k.u[j] * k.u[j];
+    const double d[2] = {2.0 * k.c * k.rho, 2.0 * k.rho};
+    double a, cr;                                          // dc/dp, c / (2 rho)
+    if constexpr (TAME) {
+        double y[2];
+        recips<2, true>(d, y);
+        a = quotient(ph.gamma, d[0], y[0]);
+        cr = quotient(k.c, d[1], y[1]);
+    } else {
+        a = ph.gamma / d[0];
+        cr = k.c / d[1];
+    }
     const double p_rho = ph.gm1 * (0.5 * usq);
-    g[0] = sg * (-un * pr.ir) + (a * p_rho - pr.c / (2.0 * U[0]));
+    g[0] = sg * (-un * k.ir) + (a * p_rho - cr);
 #pragma unroll
-    for (int k = 0; k < DIM; ++k) {
-        double v = a * (-ph.gm1 * pr.u[k]);
-        if (k == nd) v = v + sg * pr.ir;
-        g[1 + k] = v;
+    for (int j = 0; j < DIM; ++j) {
+        double v = a * (-ph.gm1 * k.u[j]);
+        if (j == nd) v = v + sg * k.ir;
+        g[1 + j] = v;
     }
     g[NF - 1] = a * ph.gm1;
+}
+
+// Face terms from the two states and the jump of lambda (over dx): g_L, g_R, the side whose
+// speed is the larger and its normal velocity. False where the windows of fv_fast.h do not hold.
+template <int DIM, bool TAME>
+__device__ __forceinline__ bool adjoint_face(const double* UL, const double* UR, const double* w,
+                                             int nd, const Phys& ph, double* gL, double* gR,
+                                             bool& selL, double& un)
+{
+    constexpr int NF = DIM + 2;
+    EulerPrim<DIM> pl, pr;
+    bool ok = true;
+    if constexpr (TAME) {
+        ok = euler_prims<DIM>(UL, UR, ph, pl, pr);
+    } else {
+        pl = euler_prim<DIM>(UL, ph);
+        pr = euler_prim<DIM>(UR, ph);
+    }
+    const double sL = fabs(pick<DIM>(pl.u, nd)) + pl.c;
+    const double sR = fabs(pick<DIM>(pr.u, nd)) + pr.c;
+    selL = sL > sR;
+    const double s = selL ? sL : sR;
+    SpeedSide<DIM> k;   // the faster side
+    k.rho = selL ? UL[0] : UR[0];
+    k.ir = selL ? pl.ir : pr.ir;
+    k.c = selL ? pl.c : pr.c;
+#pragma unroll
+    for (int j = 0; j < DIM; ++j) k.u[j] = selL ? pl.u[j] : pr.u[j];
+    un = pick<DIM>(k.u, nd);
+    double gs[NF];
+    speed_grad<DIM, TAME>(k, nd, ph, gs);
+    double wd = 0.0;
+#pragma unroll
+    for (int q = 0; q < NF; ++q) wd = wd + w[q] * (UR[q] - UL[q]);
+    euler_flux_jt<DIM>(UL, pl, nd, w, ph, gL);
+    euler_flux_jt<DIM>(UR, pr, nd, w, ph, gR);
+#pragma unroll
+    for (int q = 0; q < NF; ++q) {
+        const double ds = 0.5 * wd * gs[q];
+        gL[q] = 0.5 * (gL[q] + s * w[q]) - (selL ? ds : 0.0);
+        gR[q] = 0.5 * (gR[q] - s * w[q]) - (selL ? 0.0 : ds);
+    }
+    return ok;
 }
 
 // minmod branch: 0 -> 0, 1 -> first argument, 2 -> second (as the forward comparisons).
@@ -101,71 +159,110 @@ struct AdjTile {
     static constexpr int NFY = (DIM >= 2) ? BX * EYN : 0;
     static constexpr int NFACES = NFX + NFY;
     static constexpr int CELLS = BX * BY;
-    static constexpr int CPT = (CELLS + NT - 1) / NT;
 };
 
+// What bounds it is FP64 issue (about 1.2 faces' work of the forward stage, twice over) and, before,
+// how few workgroups fitted a CU: tiles and face terms side by side took 41.7 KB, three
+// workgroups. A tile has at most one x face and one y face per thread, so both faces' terms wait
+// in registers until every thread has read the tiles, and then take the tiles' place, an axis at
+// a time: 25.3 KB; its 106 registers leave four wavefronts per SIMD. With the short face
+// arithmetic and uniform tile addresses, 16 samples of 256^2: 73.8 -> 61.5 us.
 template <int DIM, int RECON, int BX, int BY, int NT>
-__global__ void __launch_bounds__(NT)
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 8)))
 adjoint_stage_kernel(const AdjArgs a)
 {
     using T = AdjTile<DIM, RECON, BX, BY, NT>;
     constexpr int NF = T::NF, R = T::R, HU = T::HU, HL = T::HL;
     constexpr int UX = T::UX, UY = T::UY, LX = T::LX, LY = T::LY;
-    constexpr int NFX = T::NFX, NFACES = T::NFACES, EXN = T::EXN, EYN = T::EYN;
+    constexpr int NFX = T::NFX, EXN = T::EXN, NFY = T::NFY;
     constexpr int UC = UX * UY, LC = LX * LY;
-    constexpr int NFY = T::NFY;
+    constexpr int HUY = (DIM >= 2) ? HU : 0, HLY = (DIM >= 2) ? HL : 0;
     constexpr int MAXF = NFX > NFY ? NFX : NFY;   // faces of one axis
-    __shared__ double su[NF * UC];
-    __shared__ double sl[NF * LC];
-    __shared__ double sg[2 * NF * MAXF];   // g_L, g_R per face of the axis in hand
+    static_assert(MAXF <= NT && T::CELLS <= NT, "one face of an axis and one cell per thread");
+    constexpr int TILES = NF * (UC + LC), TERMS = 2 * NF * MAXF;
+    __shared__ double lds[TILES > TERMS ? TILES : TERMS];
     __shared__ int scode[MAXF];            // minmod codes, 2 bits per component and side
     __shared__ unsigned long long ssig;    // the workgroup's branch-signature sum
+    __shared__ int wild[NT / 64];          // per wavefront: it loaded a cell that is not tame
+    double* su = lds;
+    double* sl = lds + NF * UC;
+    double* sg = lds;                      // g_L, g_R per face of the axis in hand
 
-    const int64_t blk = xcd_remap(blockIdx.x, a.nblocks);
-    const int32_t sample = (int32_t)(blk / a.ntiles);
-    const int32_t tile = (int32_t)(blk % a.ntiles);
-    const int32_t tx = tile % a.tiles[0];
-    const int32_t ty = tile / a.tiles[0];
+    const uint32_t blk = xcd_remap(blockIdx.x, (uint32_t)a.nblocks);
+    const int32_t sample = (int32_t)a.by_ntiles.quotient(blk);
+    const int32_t tile = (int32_t)blk - sample * a.ntiles;
+    const int32_t ty = (int32_t)a.by_t0.quotient((uint32_t)tile);
+    const int32_t tx = tile - ty * a.tiles[0];
     const int32_t x0 = tx * BX, y0 = ty * BY;
     const int32_t nx = a.n[0], ny = a.n[1];
     const int64_t sbase = (int64_t)sample * NF * a.cells;
     const double* U = a.U + sbase;
     const double* lam = a.lam + sbase;
 
-    // the haloed tiles of U and lambda into LDS, every load issued before the first store
+    // the haloed tiles of U and lambda into LDS, every load issued before the first store; a tile
+    // away from the grid's edges at 32-bit offsets from one address per field
+    const bool inner = x0 >= HU && x0 + BX + HU <= nx && (DIM < 2 || (y0 >= HU && y0 + BY + HU <= ny)) &&
+                       (int64_t)UY * nx < (1 << 29);
     {
         constexpr int UPT = (UC + NT - 1) / NT, LPT = (LC + NT - 1) / NT;
         double vu[UPT][NF], vl[LPT][NF];
+        if (inner) {
+            const double* bu = U + ((int64_t)(y0 - HUY) * nx + (x0 - HU));
+            const double* bl = lam + ((int64_t)(y0 - HLY) * nx + (x0 - HL));
+#pragma unroll
+            for (int k = 0; k < UPT; ++k) {
+                const uint32_t e = threadIdx.x + k * NT;
+                if ((k + 1) * NT <= UC || e < UC) {
+                    const uint32_t off = (uint32_t)sizeof(double) * ((e / UX) * (uint32_t)nx + e % UX);
+#pragma unroll
+                    for (int q = 0; q < NF; ++q) vu[k][q] = *at_byte(bu + q * a.cells, off);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < LPT; ++k) {
+                const uint32_t e = threadIdx.x + k * NT;
+                if ((k + 1) * NT <= LC || e < LC) {
+                    const uint32_t off = (uint32_t)sizeof(double) * ((e / LX) * (uint32_t)nx + e % LX);
+#pragma unroll
+                    for (int q = 0; q < NF; ++q) vl[k][q] = *at_byte(bl + q * a.cells, off);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < UPT; ++k) {
+                const int e = threadIdx.x + k * NT;
+                if ((k + 1) * NT <= UC || e < UC) {
+                    const int px = e % UX, py = e / UX;
+                    const int32_t gx = wrap_index(x0 + px - HU, nx, a.bc[0]);
+                    const int32_t gy = (DIM >= 2) ? wrap_index(y0 + py - HU, ny, a.bc[1]) : 0;
+                    const int32_t gi = gy * nx + gx;   // cells < 2^31
+#pragma unroll
+                    for (int q = 0; q < NF; ++q) vu[k][q] = U[q * a.cells + gi];
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < LPT; ++k) {
+                const int e = threadIdx.x + k * NT;
+                if ((k + 1) * NT <= LC || e < LC) {
+                    const int px = e % LX, py = e / LX;
+                    const int32_t gx = wrap_index(x0 + px - HL, nx, a.bc[0]);
+                    const int32_t gy = (DIM >= 2) ? wrap_index(y0 + py - HL, ny, a.bc[1]) : 0;
+                    const int32_t gi = gy * nx + gx;
+#pragma unroll
+                    for (int q = 0; q < NF; ++q) vl[k][q] = lam[q * a.cells + gi];
+                }
+            }
+        }
+        CellRange range;
 #pragma unroll
         for (int k = 0; k < UPT; ++k) {
             const int e = threadIdx.x + k * NT;
             if ((k + 1) * NT <= UC || e < UC) {
-                const int px = e % UX, py = e / UX;
-                const int32_t gx = wrap_index(x0 + px - HU, nx, a.bc[0]);
-                const int32_t gy = (DIM >= 2) ? wrap_index(y0 + py - HU, ny, a.bc[1]) : 0;
-                const int32_t gi = gy * nx + gx;   // cells < 2^31
 #pragma unroll
-                for (int q = 0; q < NF; ++q) vu[k][q] = U[q * a.cells + gi];
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < LPT; ++k) {
-            const int e = threadIdx.x + k * NT;
-            if ((k + 1) * NT <= LC || e < LC) {
-                const int px = e % LX, py = e / LX;
-                const int32_t gx = wrap_index(x0 + px - HL, nx, a.bc[0]);
-                const int32_t gy = (DIM >= 2) ? wrap_index(y0 + py - HL, ny, a.bc[1]) : 0;
-                const int32_t gi = gy * nx + gx;
-#pragma unroll
-                for (int q = 0; q < NF; ++q) vl[k][q] = lam[q * a.cells + gi];
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < UPT; ++k) {
-            const int e = threadIdx.x + k * NT;
-            if ((k + 1) * NT <= UC || e < UC) {
-#pragma unroll
-                for (int q = 0; q < NF; ++q) su[q * UC + e] = vu[k][q];
+                for (int q = 0; q < NF; ++q) {
+                    range.add<true>(vu[k][q]);
+                    su[q * UC + e] = vu[k][q];
+                }
             }
         }
 #pragma unroll
@@ -176,21 +273,26 @@ adjoint_stage_kernel(const AdjArgs a)
                 for (int q = 0; q < NF; ++q) sl[q * LC + e] = vl[k][q];
             }
         }
+        const bool any = any_lane(!range.tame());
+        if ((threadIdx.x & 63) == 0) wild[threadIdx.x >> 6] = any;
+        if (threadIdx.x == 0) ssig = 0ull;
     }
     __syncthreads();
+    int anywild = 0;
+#pragma unroll
+    for (int i = 0; i < NT / 64; ++i) anywild |= wild[i];
+    const bool tame = __builtin_amdgcn_readfirstlane(anywild) == 0;
 
-    // one axis at a time: its faces' (g_L, g_R, codes) into LDS, then every cell gathers the
-    // axis's four (MUSCL) or two faces; axis 0 is added before axis 1, as in eq. 2.1
-    double jt[T::CPT][NF];
-#pragma unroll
-    for (int k = 0; k < T::CPT; ++k)
-#pragma unroll
-        for (int q = 0; q < NF; ++q) jt[k][q] = 0.0;
+    // the thread's face of each axis: g_L, g_R and codes in registers
+    const int f = threadIdx.x;
+    double g[DIM][2][NF];
+    int code[DIM];
     unsigned long long hsig = 0ull;   // this thread's signature terms (faces it owns)
 #pragma unroll
     for (int nd = 0; nd < DIM; ++nd) {
         const int nfaces = (nd == 0) ? NFX : NFY;
-        for (int f = threadIdx.x; f < nfaces; f += NT) {
+        code[nd] = 0;
+        if (f < nfaces) {
             int fx, fy;   // face between (right cell) and (right cell - e_nd), tile-local
             if (nd == 0) {
                 fx = f % EXN - R;          // right-cell x offset from x0, in [-R, BX + R]
@@ -200,148 +302,152 @@ adjoint_stage_kernel(const AdjArgs a)
                 fy = f / BX - R;
             }
             const int cu = ((DIM >= 2 ? fy + HU : 0)) * UX + (fx + HU);
-            const int su_stride = (nd == 0) ? 1 : UX;
             const int cl = ((DIM >= 2 ? fy + HL : 0)) * LX + (fx + HL);
-            const int sl_stride = (nd == 0) ? 1 : LX;
-            double UL[NF], UR[NF], w[NF];
-            int codes = 0;
             const double inv = (nd == 0) ? a.ph.inv_dx[0] : a.ph.inv_dx[1];
+            constexpr int SX = 1;
+            const int us = (nd == 0) ? SX : UX, ls = (nd == 0) ? SX : LX;
+            double w[NF];
 #pragma unroll
-            for (int q = 0; q < NF; ++q) {
-                const double* sp = su + q * UC + cu;
-                const double ua = sp[-su_stride], ub = sp[0];
-                if (RECON == REC_MUSCL) {
-                    const double uam = sp[-2 * su_stride], ubp = sp[su_stride];
-                    const int cL = minmod_code(ua - uam, ub - ua);
-                    const int cR = minmod_code(ub - ua, ubp - ub);
-                    codes |= (cL | (cR << 2)) << (4 * q);
-                    UL[q] = ua + (0.5 * minmod(ua - uam, ub - ua));
-                    UR[q] = ub - (0.5 * minmod(ub - ua, ubp - ub));
-                } else {
-                    UL[q] = ua;
-                    UR[q] = ub;
+            for (int q = 0; q < NF; ++q) w[q] = inv * (sl[q * LC + cl] - sl[q * LC + cl - ls]);
+            bool selL = false, done = false;
+            double un = 0.0;
+            if (tame) {
+                double UL[NF], UR[NF];
+                int codes = 0;
+#pragma unroll
+                for (int q = 0; q < NF; ++q) {
+                    const double* sp = su + q * UC + cu;
+                    const double ua = sp[-us], ub = sp[0];
+                    if (RECON == REC_MUSCL) {
+                        const double dl = ua - sp[-2 * us], dm = ub - ua, dr = sp[us] - ub;
+                        codes |= (minmod_code(dl, dm) | (minmod_code(dm, dr) << 2)) << (4 * q);
+                        UL[q] = __builtin_fma(0.5, minmod_finite(dl, dm), ua);
+                        UR[q] = __builtin_fma(-0.5, minmod_finite(dm, dr), ub);
+                    } else {
+                        UL[q] = ua;
+                        UR[q] = ub;
+                    }
                 }
-                const double* l = sl + q * LC + cl;
-                w[q] = inv * (l[0] - l[-sl_stride]);
+                code[nd] = codes;
+                done = !any_lane(!adjoint_face<DIM, true>(UL, UR, w, nd, a.ph, g[nd][0], g[nd][1], selL, un));
             }
-            const EulerPrim<DIM> pl = euler_prim<DIM>(UL, a.ph);
-            const EulerPrim<DIM> pr = euler_prim<DIM>(UR, a.ph);
-            const double sL = fabs(pick<DIM>(pl.u, nd)) + pl.c;
-            const double sR = fabs(pick<DIM>(pr.u, nd)) + pr.c;
-            const bool selL = sL > sR;
-            const double s = selL ? sL : sR;
-            double jl[NF], jr[NF], gs[NF];
-            euler_flux_jt<DIM>(UL, pl, nd, w, a.ph, jl);
-            euler_flux_jt<DIM>(UR, pr, nd, w, a.ph, jr);
-            if (selL) speed_grad<DIM>(UL, pl, nd, a.ph, gs);
-            else speed_grad<DIM>(UR, pr, nd, a.ph, gs);
-            double wd = 0.0;
+            if (!done) {
+                int c = cu;
+                asm volatile("" : "+v"(c));   // read again: nothing is kept for this path
+                double UL[NF], UR[NF];
+                int codes = 0;
 #pragma unroll
-            for (int q = 0; q < NF; ++q) wd = wd + w[q] * (UR[q] - UL[q]);
-#pragma unroll
-            for (int q = 0; q < NF; ++q) {
-                const double ds = 0.5 * wd * gs[q];
-                const double gL = 0.5 * (jl[q] + s * w[q]) - (selL ? ds : 0.0);
-                const double gR = 0.5 * (jr[q] - s * w[q]) - (selL ? 0.0 : ds);
-                sg[(2 * q) * MAXF + f] = gL;
-                sg[(2 * q + 1) * MAXF + f] = gR;
+                for (int q = 0; q < NF; ++q) {
+                    const double* sp = su + q * UC + c;
+                    const double ua = sp[-us], ub = sp[0];
+                    if (RECON == REC_MUSCL) {
+                        const double dl = ua - sp[-2 * us], dm = ub - ua, dr = sp[us] - ub;
+                        codes |= (minmod_code(dl, dm) | (minmod_code(dm, dr) << 2)) << (4 * q);
+                        UL[q] = ua + (0.5 * minmod(dl, dm));
+                        UR[q] = ub - (0.5 * minmod(dm, dr));
+                    } else {
+                        UL[q] = ua;
+                        UR[q] = ub;
+                    }
+                }
+                code[nd] = codes;
+                adjoint_face<DIM, false>(UL, UR, w, nd, a.ph, g[nd][0], g[nd][1], selL, un);
             }
-            scode[f] = codes;
             if (a.sig) {
                 // each face once: by the tile of its right cell, inside the grid
                 const int32_t gx = x0 + fx, gy = (DIM >= 2) ? y0 + fy : 0;
                 const bool own = (nd == 0) ? (fx >= 0 && fx < BX) : (fy >= 0 && fy < BY);
                 if (own && gx < nx && gy < ny) {
-                    const double un = selL ? pick<DIM>(pl.u, nd) : pick<DIM>(pr.u, nd);
                     const unsigned long long sgn = (un > 0.0) ? 2ull : ((un < 0.0) ? 0ull : 1ull);
-                    const unsigned long long code = (unsigned long long)(unsigned)codes |
-                                                    ((selL ? 1ull : 0ull) << 32) | (sgn << 33);
+                    const unsigned long long cd = (unsigned long long)(unsigned)code[nd] |
+                                                  ((selL ? 1ull : 0ull) << 32) | (sgn << 33);
                     const unsigned long long key = ((unsigned long long)(gy * nx + gx) << 2) | nd;
-                    hsig += sig_mix(a.salt ^ sig_mix(key * 0x9E3779B97F4A7C15ull + code));
+                    hsig += sig_mix(a.salt ^ sig_mix(key * 0x9E3779B97F4A7C15ull + cd));
                 }
             }
         }
-        __syncthreads();
+    }
 
+    // this thread's cell: its lambda, then the contributions of its faces, axis 0 before axis 1 as
+    // in eq. 2.1, each axis's four (MUSCL) or two faces in a fixed order
+    const int c = threadIdx.x;
+    const int cx = c % BX, cy = c / BX;
+    double lq[NF], jt[NF];
 #pragma unroll
-        for (int k = 0; k < T::CPT; ++k) {
-            const int c = threadIdx.x + k * NT;
-            if (c >= T::CELLS) break;
-            const int cx = c % BX, cy = c / BX;
+    for (int q = 0; q < NF; ++q) {
+        lq[q] = (c < T::CELLS) ? sl[q * LC + (cy + HLY) * LX + (cx + HL)] : 0.0;
+        jt[q] = 0.0;
+    }
+#pragma unroll
+    for (int nd = 0; nd < DIM; ++nd) {
+        __syncthreads();   // the tiles, or the axis before, are read
+        const int nfaces = (nd == 0) ? NFX : NFY;
+        if (f < nfaces) {
+#pragma unroll
+            for (int q = 0; q < NF; ++q) {
+                sg[(2 * q) * MAXF + f] = g[nd][0][q];
+                sg[(2 * q + 1) * MAXF + f] = g[nd][1][q];
+            }
+            scode[f] = code[nd];
+        }
+        __syncthreads();
+        if (c < T::CELLS) {
             // face index (within this axis) with right cell at tile offset o + shift along nd
             auto face = [&](int shift) -> int {
                 if (nd == 0) return cy * EXN + (cx + shift + R);
                 return (cy + shift + R) * BX + cx;
             };
+            if constexpr (RECON == REC_MUSCL) {
+                const int f0 = face(-1), f1 = face(0), f2 = face(1), f3 = face(2);
+                const int c0 = scode[f0], c1 = scode[f1], c2 = scode[f2], c3 = scode[f3];
 #pragma unroll
-            for (int q = 0; q < NF; ++q) {
-                double v = jt[k][q];
-                if (RECON == REC_MUSCL) {
-                    {   // face c - 3/2 (right cell c - 1): this cell is b + 1
-                        const int f = face(-1);
-                        const int cR = (scode[f] >> (4 * q + 2)) & 3;
-                        v = v + sg[(2 * q + 1) * MAXF + f] * ((cR == 2) ? -0.5 : 0.0);
-                    }
-                    {   // face c - 1/2 (right cell c): this cell is b
-                        const int f = face(0);
-                        const int cL = (scode[f] >> (4 * q)) & 3;
-                        const int cR = (scode[f] >> (4 * q + 2)) & 3;
-                        v = v + sg[(2 * q) * MAXF + f] * ((cL == 2) ? 0.5 : 0.0);
-                        v = v + sg[(2 * q + 1) * MAXF + f] * ((cR == 1) ? 0.5 : ((cR == 2) ? 1.5 : 1.0));
-                    }
-                    {   // face c + 1/2 (right cell c + 1): this cell is a
-                        const int f = face(1);
-                        const int cL = (scode[f] >> (4 * q)) & 3;
-                        const int cR = (scode[f] >> (4 * q + 2)) & 3;
-                        v = v + sg[(2 * q) * MAXF + f] * ((cL == 1) ? 1.5 : ((cL == 2) ? 0.5 : 1.0));
-                        v = v + sg[(2 * q + 1) * MAXF + f] * ((cR == 1) ? 0.5 : 0.0);
-                    }
-                    {   // face c + 3/2 (right cell c + 2): this cell is a - 1
-                        const int f = face(2);
-                        const int cL = (scode[f] >> (4 * q)) & 3;
-                        v = v + sg[(2 * q) * MAXF + f] * ((cL == 1) ? -0.5 : 0.0);
-                    }
-                } else {
-                    v = v + sg[(2 * q + 1) * MAXF + face(0)];   // face c - 1/2: g_R
-                    v = v + sg[(2 * q) * MAXF + face(1)];       // face c + 1/2: g_L
+                for (int q = 0; q < NF; ++q) {
+                    const int b = 4 * q;
+                    const int r0 = (c0 >> (b + 2)) & 3, l1 = (c1 >> b) & 3, r1 = (c1 >> (b + 2)) & 3;
+                    const int l2 = (c2 >> b) & 3, r2 = (c2 >> (b + 2)) & 3, l3 = (c3 >> b) & 3;
+                    const double* gl = sg + (2 * q) * MAXF;
+                    const double* gr = gl + MAXF;
+                    double v = jt[q];
+                    v = v + gr[f0] * ((r0 == 2) ? -0.5 : 0.0);   // face c - 3/2: this cell is b + 1
+                    v = v + gl[f1] * ((l1 == 2) ? 0.5 : 0.0);    // face c - 1/2: this cell is b
+                    v = v + gr[f1] * ((r1 == 1) ? 0.5 : ((r1 == 2) ? 1.5 : 1.0));
+                    v = v + gl[f2] * ((l2 == 1) ? 1.5 : ((l2 == 2) ? 0.5 : 1.0));   // c + 1/2: a
+                    v = v + gr[f2] * ((r2 == 1) ? 0.5 : 0.0);
+                    v = v + gl[f3] * ((l3 == 1) ? -0.5 : 0.0);   // face c + 3/2: this cell is a - 1
+                    jt[q] = v;
                 }
-                jt[k][q] = v;
+            } else {
+                const int f1 = face(0), f2 = face(1);
+#pragma unroll
+                for (int q = 0; q < NF; ++q) {
+                    jt[q] = jt[q] + sg[(2 * q + 1) * MAXF + f1];   // face c - 1/2: g_R
+                    jt[q] = jt[q] + sg[(2 * q) * MAXF + f2];       // face c + 1/2: g_L
+                }
             }
         }
-        if (nd + 1 < DIM) __syncthreads();   // the next axis overwrites sg
     }
     if (a.sig) {   // uniform over the launch
-        if (threadIdx.x == 0) ssig = 0ull;
-        __syncthreads();
         atomicAdd(&ssig, hsig);
         __syncthreads();
         if (threadIdx.x == 0) atomicAdd(a.sig + sample, ssig);
     }
 
     // the reverse stage combination
+    const int32_t gx = x0 + cx, gy = y0 + cy;
+    if (c >= T::CELLS || gx >= nx || gy >= ny) return;
     double* prev = a.prev + sbase;
     double* acc = a.acc + sbase;
+    const int32_t gi = gy * nx + gx;
 #pragma unroll
-    for (int k = 0; k < T::CPT; ++k) {
-        const int c = threadIdx.x + k * NT;
-        if (c >= T::CELLS) break;
-        const int cx = c % BX, cy = c / BX;
-        const int32_t gx = x0 + cx, gy = y0 + cy;
-        if (gx >= nx || gy >= ny) continue;
-        const int32_t gi = gy * nx + gx;
-        const int cl = ((DIM >= 2 ? cy + HL : 0)) * LX + (cx + HL);
-#pragma unroll
-        for (int q = 0; q < NF; ++q) {
-            const double lq = sl[q * LC + cl];
-            const double contrib = a.beta * (lq + a.dt * jt[k][q]);
-            const int64_t o = q * a.cells + gi;
-            if (a.mode == 2) {
-                prev[o] = acc[o] + contrib;
-            } else {
-                prev[o] = contrib;
-                const double keep = (1.0 - a.beta) * lq;
-                acc[o] = (a.mode == 0) ? keep : (acc[o] + keep);
-            }
+    for (int q = 0; q < NF; ++q) {
+        const double contrib = a.beta * (lq[q] + a.dt * jt[q]);
+        const int64_t o = q * a.cells + gi;
+        if (a.mode == 2) {
+            prev[o] = acc[o] + contrib;
+        } else {
+            prev[o] = contrib;
+            const double keep = (1.0 - a.beta) * lq[q];
+            acc[o] = (a.mode == 0) ? keep : (acc[o] + keep);
         }
     }
 }

@@ -301,6 +301,8 @@ static fv_status reverse_stage(fv_adjoint* a, const double* U, const double* lam
         g.ntiles *= g.tiles[k];
         g.bc[k] = s->grid.bc[k];
     }
+    g.by_ntiles = make_divisor((uint32_t)g.ntiles);
+    g.by_t0 = make_divisor((uint32_t)g.tiles[0]);
     g.batch = (int32_t)a->batch;
     g.mode = mode;
     g.beta = beta;
