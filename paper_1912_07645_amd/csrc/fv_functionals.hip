@@ -15,8 +15,9 @@
 // the periodic grid, p in {1, 2}, over the cube shell A_h = {o : max_k |o_k| = h} or the ball
 // shell {o : (h - 1)^2 < |o|^2 <= h^2}. One workgroup takes one tile of one quantity of one
 // sample: the quantity over the tile and a periodic halo of max_h cells on every active axis
-// goes into LDS, then every thread walks the shells h = 1..max_h of its cell (all threads take
-// the same offsets, so the shell tests are uniform) and the workgroup sums its cells per h
+// goes into LDS, then every thread walks the shells h = 1..max_h of its cells (all threads take
+// the same offsets, so the shell tests are uniform; one offset of every pair o, -o, whose sums
+// over the periodic grid are equal) and the workgroup sums its cells per h
 // (wavefront shuffles, then the wavefronts in order). A second pass adds the tiles in order
 // and divides. Sums run in another order than the definition's, so results agree with it to
 // rounding (relative 1e-12 and better in the tests), not bit for bit.
@@ -24,19 +25,26 @@
 #include <vector>
 
 #include "fv_host.h"
+#include "fv_stage.h"
 
 namespace fvk {
 
 constexpr int kFnThreads = 256;
 constexpr int kShellMaxH = 64;
+constexpr int kShellTile2 = 64;    // side of the register-tiled 2D shell kernel's tile
+constexpr int kShellMaxH2 = 16;    // and its largest radius (61 KB of LDS; beyond, one cell per thread)
 
 // kind: 0 the field itself; 1 Euler (momenta over rho); 2 shallow water (momenta over h);
 // 3 ideal MHD (the three momenta over rho).
+__device__ __forceinline__ bool quantity_divides(int kind, int nf, int qi)
+{
+    return !(kind == 0 || qi == 0 || (kind == 1 && qi == nf - 1) || (kind == 3 && qi > 3));
+}
+
 __device__ __forceinline__ double quantity_at(const double* U, int64_t cells, int nf, int kind,
                                               int64_t c, int qi)
 {
-    if (kind == 0 || qi == 0 || (kind == 1 && qi == nf - 1) || (kind == 3 && qi > 3))
-        return U[(int64_t)qi * cells + c];
+    if (!quantity_divides(kind, nf, qi)) return U[(int64_t)qi * cells + c];
     const double ir = 1.0 / U[c];
     return U[(int64_t)qi * cells + c] * ir;
 }
@@ -110,12 +118,18 @@ __device__ __forceinline__ bool in_ball_shell(int ox, int oy, int oz, int h)
     return (h - 1) * (h - 1) < r2 && r2 <= h * h;
 }
 
+// acc + |d|^P
 template <int P>
-__device__ __forceinline__ double shell_term(double d)
+__device__ __forceinline__ double shell_add(double acc, double d)
 {
-    return (P == 1) ? fabs(d) : (d * d);
+    return (P == 1) ? acc + fabs(d) : __builtin_fma(d, d, acc);
 }
 
+// Sums over half a shell. On the periodic grid sum_x |q(x + o) - q(x)|^p is the same for o and -o,
+// so of every such pair one offset is taken (the first nonzero of oz, oy, ox positive), and the
+// sum over the shell is twice that over its half: half the terms.
+
+// One cell per thread (1D, 3D, and 2D radii beyond the register-tiled kernel below).
 template <int DIM, int P>
 __global__ void __launch_bounds__(kFnThreads) shell_kernel(const ShellArgs a)
 {
@@ -155,19 +169,20 @@ __global__ void __launch_bounds__(kFnThreads) shell_kernel(const ShellArgs a)
     for (int h = 1; h <= H; ++h) {
         const int hy = (DIM >= 2) ? h : 0, hz = (DIM >= 3) ? h : 0;
         double acc = 0.0;
-        for (int oz = -hz; oz <= hz; ++oz)
-            for (int oy = -hy; oy <= hy; ++oy) {
+        for (int oz = 0; oz <= hz; ++oz)
+            for (int oy = (oz == 0) ? 0 : -hy; oy <= hy; ++oy) {
                 const double* row = lq + lc + (oz * PY + oy) * PX;
+                const bool own = oz == 0 && oy == 0;   // the cell's own row: to the right only
                 if (a.ball) {
-                    for (int ox = -h; ox <= h; ++ox)
-                        if (in_ball_shell(ox, oy, oz, h)) acc = acc + shell_term<P>(row[ox] - q0);
-                } else if ((DIM >= 2 && (oy == -h || oy == h)) || (DIM >= 3 && (oz == -h || oz == h))) {
+                    for (int ox = own ? 1 : -h; ox <= h; ++ox)
+                        if (in_ball_shell(ox, oy, oz, h)) acc = shell_add<P>(acc, row[ox] - q0);
+                } else if ((DIM >= 2 && (oy == -h || oy == h)) || (DIM >= 3 && oz == h)) {
                     // a row on a face of the cube (only active axes have faces)
-                    for (int ox = -h; ox <= h; ++ox) acc = acc + shell_term<P>(row[ox] - q0);
+                    for (int ox = -h; ox <= h; ++ox) acc = shell_add<P>(acc, row[ox] - q0);
                 } else {
                     // an inner row of the cube: only its two ends are on the shell
-                    acc = acc + shell_term<P>(row[-h] - q0);
-                    acc = acc + shell_term<P>(row[h] - q0);
+                    if (!own) acc = shell_add<P>(acc, row[-h] - q0);
+                    acc = shell_add<P>(acc, row[h] - q0);
                 }
             }
         acc = inside ? acc : 0.0;
@@ -183,12 +198,208 @@ __global__ void __launch_bounds__(kFnThreads) shell_kernel(const ShellArgs a)
     }
 }
 
+// 2D, radii up to HM: 64 x 64 cells to a workgroup, 4 x 4 to a thread. What bounded one cell per
+// thread was LDS, a read for every term. Here a thread slides a window of four values along a row
+// of offsets (or, for the cube's two side columns, along a column): one read serves the terms of
+// four cells, 0.3 reads per term for a cube of radius 8, and the FP64 pipe (a subtraction and a
+// fused multiply-add per term) is the bound. Rows are stored by column modulo 4, so that the
+// lanes of a row, four columns apart, read neighbouring slots. The halo is 16 rows less (offsets
+// point up), and 1.4 cells are staged per cell instead of 4. 64 samples of 256^2, cube shells to
+// radius 8: 1030 -> 282 us
+// (18 T operations/s; the FP64 pipe sustains about 30 under its power limit).
+template <int P, bool BALL, int HM>
+__global__ void __launch_bounds__(kFnThreads) __attribute__((amdgpu_waves_per_eu(3, 8)))
+shell2d_kernel(const ShellArgs a)
+{
+    constexpr int T = kShellTile2, PX = T + 2 * HM, Q = PX / 4;
+    static_assert(HM % 4 == 0 && T == 64 && kFnThreads == 256, "4 x 4 cells per thread");
+    extern __shared__ double lds[];
+    const int H = a.H, rows = T + H;
+    double* wsum = lds + rows * PX;         // [waves][H]
+
+    const int64_t blk = blockIdx.x;
+    const int32_t tile = (int32_t)(blk % a.ntiles);
+    const int64_t sq = blk / a.ntiles;      // sample * nq + quantity
+    const int qi = (int)(sq % a.nq);
+    const double* U = a.state + (sq / a.nq) * a.nf * a.cells;
+    const int32_t x0 = (tile % a.tiles[0]) * T, y0 = (tile / a.tiles[0]) * T;
+
+    // the quantity over the tile and its halo: eight values at a time are requested before the
+    // first is used
+    const bool divide = quantity_divides(a.kind, a.nf, qi);   // uniform
+    const double* F = U + (int64_t)qi * a.cells;
+    constexpr int D = 8;
+    for (int e0 = threadIdx.x; e0 < rows * PX; e0 += D * kFnThreads) {
+        double v[D], d[D];
+#pragma unroll
+        for (int i = 0; i < D; ++i) {
+            const int e = e0 + i * kFnThreads;
+            const int px = e % PX, py = e / PX;
+            const int32_t gx = wrap_index(x0 + px - HM, a.n[0], BC_PERIODIC);
+            const int32_t gy = wrap_index(y0 + py, a.n[1], BC_PERIODIC);
+            const int32_t c = gy * a.n[0] + gx;   // cells < 2^31
+            v[i] = F[c];
+            d[i] = divide ? U[c] : 1.0;
+        }
+#pragma unroll
+        for (int i = 0; i < D; ++i) {
+            const int e = e0 + i * kFnThreads;
+            const int px = e % PX, py = e / PX;
+            if (e < rows * PX)
+                lds[py * PX + (px & 3) * Q + (px >> 2)] = divide ? v[i] * (1.0 / d[i]) : v[i];
+        }
+    }
+    __syncthreads();
+
+    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+    const double* own = lds + 4 * ty * PX + tx;
+    // slot of the value `col` columns right of the thread's first cell
+    auto slot = [&](int col) {
+        const int k = HM + col;
+        return (k & 3) * Q + (k >> 2);
+    };
+    double q[4][4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) q[r][j] = own[r * PX + slot(j)];
+    bool in_x[4], in_y[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        in_x[i] = x0 + 4 * tx + i < a.n[0];
+        in_y[i] = y0 + 4 * ty + i < a.n[1];
+    }
+    double acc[4][4];
+    // the offsets (ox, oy), ox = lo..hi, of every cell: a window w[row] of four columns that
+    // slides to the right, all four rows at a time
+    auto along_row = [&](int oy, int lo, int hi) {
+        const double* base = own + oy * PX;
+        double w[4][4];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const double* p = base + slot(lo + j);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) w[r][j] = p[r * PX];
+        }
+        int ox = lo;
+#pragma unroll 1
+        for (; ox + 3 <= hi; ox += 4) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const double* p = base + slot(ox + s + 3);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    w[r][(s + 3) & 3] = p[r * PX];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        acc[r][j] = shell_add<P>(acc[r][j], w[r][(s + j) & 3] - q[r][j]);
+                }
+            }
+        }
+#pragma unroll 1
+        for (; ox <= hi; ++ox) {
+            const double* p = base + slot(ox + 3);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                w[r][3] = p[r * PX];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[r][j] = shell_add<P>(acc[r][j], w[r][j] - q[r][j]);
+#pragma unroll
+                for (int j = 0; j < 3; ++j) w[r][j] = w[r][j + 1];
+            }
+        }
+    };
+    // the offsets (ox, oy), oy = 1..hi, of every cell: a window w[column] of four rows that slides up
+    auto along_column = [&](int ox, int hi) {
+        const double* p[4];
+        double w[4][4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            p[j] = own + PX + slot(ox + j);
+#pragma unroll
+            for (int r = 0; r < 3; ++r) w[j][r] = p[j][r * PX];
+        }
+        int oy = 1;
+#pragma unroll 1
+        for (; oy + 3 <= hi; oy += 4) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    w[j][(s + 3) & 3] = p[j][(s + 3) * PX];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        acc[r][j] = shell_add<P>(acc[r][j], w[j][(s + r) & 3] - q[r][j]);
+                }
+                p[j] += 4 * PX;
+            }
+        }
+#pragma unroll 1
+        for (; oy <= hi; ++oy) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                w[j][3] = p[j][3 * PX];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[r][j] = shell_add<P>(acc[r][j], w[j][r] - q[r][j]);
+#pragma unroll
+                for (int r = 0; r < 3; ++r) w[j][r] = w[j][r + 1];
+                p[j] += PX;
+            }
+        }
+    };
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll 1
+    for (int h = 1; h <= H; ++h) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[r][j] = 0.0;
+        if constexpr (BALL) {
+            // (h - 1)^2 < ox^2 + oy^2 <= h^2: of row oy the columns lo..hi and -hi..-lo
+            int hi = h, lo = h;
+#pragma unroll 1
+            for (int oy = 0; oy <= h; ++oy) {
+                while (hi * hi > h * h - oy * oy) --hi;
+                const int inner = (h - 1) * (h - 1) - oy * oy;
+                if (inner < 0) {
+                    along_row(oy, -hi, hi);
+                } else {
+                    while (lo > 1 && (lo - 1) * (lo - 1) > inner) --lo;
+                    if (lo <= hi) {
+                        along_row(oy, lo, hi);
+                        if (oy > 0) along_row(oy, -hi, -lo);
+                    }
+                }
+            }
+        } else {
+            along_row(h, -h, h);
+            along_column(h, h - 1);
+            along_column(-h, h - 1);
+            along_row(0, h, h);
+        }
+        double sum = 0.0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) sum = sum + ((in_x[j] && in_y[r]) ? acc[r][j] : 0.0);
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) sum = sum + __shfl_xor(sum, off, 64);
+        if (lane == 0) wsum[wave * H + (h - 1)] = sum;
+    }
+    __syncthreads();
+    for (int h = threadIdx.x; h < H; h += kFnThreads) {
+        double s = wsum[h];
+        for (int w = 1; w < kFnThreads / 64; ++w) s = s + wsum[w * H + h];
+        a.partial[(sq * H + h) * a.ntiles + tile] = s;
+    }
+}
+
 struct ShellFinishArgs {
     const double* partial;   // [rows][ntiles], row = (sample * nq + q) * H + h - 1
     int64_t rows;
     int32_t ntiles, H;
     double cells;
-    double shell[kShellMaxH];  // |A_h|
+    double shell[kShellMaxH];  // |A_h| / 2
     double* out;             // [rows]
 };
 
@@ -206,6 +417,17 @@ template <int DIM, int P>
 static void launch_shell(const ShellArgs& a, int64_t blocks, size_t lds, hipStream_t s)
 {
     hipLaunchKernelGGL((shell_kernel<DIM, P>), dim3((unsigned)blocks), dim3(kFnThreads), lds, s, a);
+}
+
+template <int HM>
+static void launch_shell2d(const ShellArgs& a, int order, int64_t blocks, hipStream_t s)
+{
+    const size_t lds = sizeof(double) * (size_t)((kShellTile2 + a.H) * (kShellTile2 + 2 * HM) + (kFnThreads / 64) * a.H);
+    const dim3 grid((unsigned)blocks), block(kFnThreads);
+    if (order == 1 && a.ball) hipLaunchKernelGGL((shell2d_kernel<1, true, HM>), grid, block, lds, s, a);
+    else if (order == 1) hipLaunchKernelGGL((shell2d_kernel<1, false, HM>), grid, block, lds, s, a);
+    else if (a.ball) hipLaunchKernelGGL((shell2d_kernel<2, true, HM>), grid, block, lds, s, a);
+    else hipLaunchKernelGGL((shell2d_kernel<2, false, HM>), grid, block, lds, s, a);
 }
 
 // Number of offsets in the shell of radius h (same membership rule as the kernel).
@@ -313,12 +535,22 @@ extern "C" fv_status fv_structure_shell(const fv_solver* s, const double* state,
     const int64_t P[3] = {T[0] + 2 * max_h, dim >= 2 ? T[1] + 2 * max_h : 1, dim >= 3 ? T[2] + 2 * max_h : 1};
     const size_t lds = sizeof(double) * (size_t)(P[0] * P[1] * P[2] + (kFnThreads / 64) * max_h);
     if (lds > 65536) return fail(FV_ENOTSUP, "max_h too large for this dimension (tile and halo exceed 64 KB of LDS)");
+    // The register-tiled kernel, where its tiles are at least a quarter full and are enough to keep
+    // the chip busy. us, one cell per thread -> 4 x 4 (4 quantities, radius 8): 64 samples of 256^2
+    // (4096 workgroups) 1096 -> 348, 64 of 40^2 (256, 39% full) 74 -> 56; 64 of 20^2 (256, 10%
+    // full) 53 -> 67, one of 64^2 (4) 45 -> 65. The one-cell kernel takes
+    // five times as long for ball shells (256^2: 4993 -> 395).
+    const int64_t tiles64 = ((s->grid.n[0] + kShellTile2 - 1) / kShellTile2) * ((s->grid.n[1] + kShellTile2 - 1) / kShellTile2);
+    const bool wide = dim == 2 && max_h <= kShellMaxH2 &&
+                      4 * s->cells >= tiles64 * kShellTile2 * kShellTile2 &&
+                      batch * num_quantities(s) * tiles64 >= (ball ? 32 : 128);
     ShellArgs a{};
     a.cells = s->cells;
     a.ntiles = 1;
     for (int k = 0; k < 3; ++k) {
+        const int tk = (wide && k < 2) ? kShellTile2 : T[k];
         a.n[k] = (int32_t)s->grid.n[k];
-        a.tiles[k] = (int32_t)((s->grid.n[k] + T[k] - 1) / T[k]);
+        a.tiles[k] = (int32_t)((s->grid.n[k] + tk - 1) / tk);
         a.ntiles *= a.tiles[k];
     }
     a.nf = s->nf;
@@ -330,7 +562,7 @@ extern "C" fv_status fv_structure_shell(const fv_solver* s, const double* state,
     f.ntiles = a.ntiles;
     f.H = max_h;
     f.cells = (double)s->cells;
-    for (int h = 1; h <= max_h; ++h) f.shell[h - 1] = (double)shell_size(dim, h, ball);
+    for (int h = 1; h <= max_h; ++h) f.shell[h - 1] = 0.5 * (double)shell_size(dim, h, ball);
     // samples per pass: partial sums of at most 2^22 doubles (32 MiB)
     const int64_t per_sample = (int64_t)a.nq * max_h * a.ntiles;
     const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>(batch, (int64_t(1) << 22) / per_sample));
@@ -346,7 +578,10 @@ extern "C" fv_status fv_structure_shell(const fv_solver* s, const double* state,
         const int64_t nb = std::min<int64_t>(chunk, batch - b0);
         a.state = state + b0 * s->nf * s->cells;
         const int64_t blocks = nb * a.nq * a.ntiles;
-        switch (dim * 10 + order) {
+        if (wide) {
+            if (max_h <= 8) launch_shell2d<8>(a, order, blocks, sm->stream);
+            else launch_shell2d<kShellMaxH2>(a, order, blocks, sm->stream);
+        } else switch (dim * 10 + order) {
             case 11: launch_shell<1, 1>(a, blocks, lds, sm->stream); break;
             case 12: launch_shell<1, 2>(a, blocks, lds, sm->stream); break;
             case 21: launch_shell<2, 1>(a, blocks, lds, sm->stream); break;
