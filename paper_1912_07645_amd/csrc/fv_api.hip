@@ -97,7 +97,6 @@ struct fv_stats {
     double* m2 = nullptr;
     double* s2mean = nullptr;
     double* s2m2 = nullptr;
-    double* qbuf = nullptr;     // quantities of a chunk of samples
     double* partial = nullptr;  // structure-function partial sums of a chunk
     int32_t chunk;
 };
@@ -1040,8 +1039,7 @@ extern "C" fv_status fv_stats_create(const fv_solver* s, int32_t max_h, fv_stats
     st->max_h = max_h;
     st->nq = s->nf;
     st->count = 0;
-    // samples per pass: with structure functions, a chunk at a time (their partial sums); lags
-    // beyond the staged kernels' reach also stage the chunk's quantities in qbuf. Without,
+    // samples per pass: with structure functions, a chunk at a time (their partial sums). Without,
     // the whole batch goes through one Welford launch
     const int64_t state_bytes = (int64_t)sizeof(double) * st->nq * s->cells;
     st->chunk = max_h > 0 ? (int32_t)std::max<int64_t>(1, std::min<int64_t>(256, (512ll << 20) / state_bytes))
@@ -1049,14 +1047,13 @@ extern "C" fv_status fv_stats_create(const fv_solver* s, int32_t max_h, fv_stats
     const size_t field = sizeof(double) * st->nq * s->cells;
     const size_t lags = sizeof(double) * st->nq * std::max(max_h, 1);
     const int32_t n32[3] = {(int32_t)s->grid.n[0], (int32_t)s->grid.n[1], (int32_t)s->grid.n[2]};
-    const int nblk = max_h > 0 ? sf_blocks_per_field(s->grid.dim, n32, max_h) : 0;
+    const int64_t nblk = max_h > 0 ? sf_units(s->grid.dim, n32, max_h) : 0;
     bool ok = hipMalloc((void**)&st->mean, field) == hipSuccess &&
               hipMalloc((void**)&st->m2, field) == hipSuccess &&
               hipMalloc((void**)&st->s2mean, lags) == hipSuccess &&
               hipMalloc((void**)&st->s2m2, lags) == hipSuccess;
     if (ok && max_h > 0)
-        ok = (sf_staged(max_h) || hipMalloc((void**)&st->qbuf, field * st->chunk) == hipSuccess) &&
-             hipMalloc((void**)&st->partial,
+        ok = hipMalloc((void**)&st->partial,
                        sizeof(double) * st->chunk * st->nq * max_h * (nblk + 1)) == hipSuccess;
     if (!ok) {
         fv_stats_destroy(st);
@@ -1099,22 +1096,14 @@ extern "C" fv_status fv_stats_accumulate(fv_stats* st, const double* state, int6
     const int qkind = quantity_kind(s);
     const int64_t per = (int64_t)s->nf * s->cells;
     int32_t n32[3] = {(int32_t)s->grid.n[0], (int32_t)s->grid.n[1], (int32_t)s->grid.n[2]};
-    const int nblk = st->max_h > 0 ? sf_blocks_per_field(s->grid.dim, n32, st->max_h) : 0;
+    const int64_t nblk = st->max_h > 0 ? sf_units(s->grid.dim, n32, st->max_h) : 0;
     const double denom = (double)s->grid.dim * (double)s->cells;
     for (int64_t b0 = 0; b0 < batch; b0 += st->chunk) {
         const int32_t nb = (int32_t)std::min<int64_t>(st->chunk, batch - b0);
         const double* chunk = state + b0 * per;
-        // the staged structure-function kernels form the quantities from the state themselves
-        const bool staged = st->max_h > 0 && sf_staged(st->max_h);
-        launch_welford(s->nf, qkind, chunk, s->cells, nb, st->count, st->mean, st->m2,
-                       (st->max_h > 0 && !staged) ? st->qbuf : nullptr, str);
+        launch_welford(s->nf, qkind, chunk, s->cells, nb, st->count, st->mean, st->m2, str);
         if (st->max_h > 0) {
-            if (staged)
-                launch_sf_partial(chunk, s->grid.dim, n32, st->nq, st->max_h, nb, qkind,
-                                  st->partial, str);
-            else
-                launch_sf_partial(st->qbuf, s->grid.dim, n32, st->nq, st->max_h, nb, -1,
-                                  st->partial, str);
+            launch_sf_partial(chunk, s->grid.dim, n32, st->nq, st->max_h, nb, qkind, st->partial, str);
             // the per-sample values follow the partials in the same allocation
             double* xs = st->partial + (size_t)st->chunk * st->nq * st->max_h * nblk;
             launch_sf_welford(st->partial, st->nq, st->max_h, nblk, nb, st->count, denom, xs,
@@ -1223,7 +1212,6 @@ extern "C" fv_status fv_stats_destroy(fv_stats* st)
     hipFree(st->m2);
     hipFree(st->s2mean);
     hipFree(st->s2m2);
-    hipFree(st->qbuf);
     hipFree(st->partial);
     delete st;
     return FV_OK;

@@ -28,19 +28,15 @@ void launch_welford_diff(int nf, int kind, const double* fine, const double* coa
                          double* m2, hipStream_t s);
 void launch_mlmc_combine(const CombineArgs& a, double* out, hipStream_t s);
 
-// Workgroups per (sample, quantity) of the structure-function pass.
-int sf_blocks_per_field(int32_t dim, const int32_t n[3], int32_t max_h);
-// qout (may be null): also write the quantity fields of the batch, [sample][quantity][cells].
+// Partial sums per (sample, quantity, lag) of the structure-function pass.
+int64_t sf_units(int32_t dim, const int32_t n[3], int32_t max_h);
 void launch_welford(int nf, int kind, const double* state, int64_t cells, int32_t batch,
-                    int64_t count0, double* mean, double* m2, double* qout, hipStream_t s);
-// Whether max_h lags run on the staged kernels, which can form the quantities themselves.
-bool sf_staged(int32_t max_h);
-// kind < 0: q holds the quantities ([sample][quantity][cells]). kind >= 0 (staged kernels
-// only): q is the state, and the quantities are formed from it as launch_welford forms them.
-void launch_sf_partial(const double* q, int32_t dim, const int32_t n[3], int32_t nq, int32_t max_h,
-                       int32_t batch, int kind, double* partial, hipStream_t s);
+                    int64_t count0, double* mean, double* m2, hipStream_t s);
+// The quantities are formed from the state as launch_welford forms them.
+void launch_sf_partial(const double* state, int32_t dim, const int32_t n[3], int32_t nq,
+                       int32_t max_h, int32_t batch, int kind, double* partial, hipStream_t s);
 // x: scratch of batch * nq * max_h doubles (S_q(h) of each sample of the chunk).
-void launch_sf_welford(const double* partial, int32_t nq, int32_t max_h, int32_t nblk,
+void launch_sf_welford(const double* partial, int32_t nq, int32_t max_h, int64_t nblk,
                        int32_t batch, int64_t count0, double denom, double* x, double* s2mean,
                        double* s2m2, hipStream_t s);
 void launch_variance(const double* m2, int64_t n, double count, double* var, hipStream_t s);

@@ -4,6 +4,7 @@
 //
 // Quantities: Euler (rho, u_1..u_dim, E) with u_k = m_k * (1 / rho); scalar: the field.
 #include "fv_stats.h"
+#include "fv_stage_y.h"
 
 #include <algorithm>
 
@@ -13,24 +14,21 @@ namespace fvk {
 // 64 cells with one wavefront per quantity (64 NF threads): each thread keeps the running
 // moments of one (cell, quantity) in registers, so a batch has NF times as many wavefronts as
 // cells / 64. The loads of the next kWelfordDepth samples are issued before the current ones
-// are processed, so each thread has that many samples' loads in flight. With qout, the
-// quantities are also written there ([sample][quantity][cells]) for the structure functions.
+// are processed, so each thread has that many samples' loads in flight.
 // KIND: 0 the field itself; 1 Euler (the momenta divided by rho); 2 shallow water (the
 // momenta divided by h); 3 ideal MHD (the three momenta divided by rho). The divisor is field
 // 0. SHARE: its own wavefront, which loads it anyway, passes each group of samples' values to
 // the other wavefronts through LDS (two buffers, one barrier per group), so every field of a
-// sample is read from memory once; otherwise each dividing wavefront loads field 0 itself.
-// The launch without qout shares (fewer bytes: 400 us against 472 us for 1024 samples of 256^2
-// Euler); the one that writes the quantities does not (there the barrier costs more than the
-// re-reads: 251 us against 216 us for 256 samples).
+// sample is read from memory once (400 us against 472 us with field 0 loaded by every dividing
+// wavefront, for 1024 samples of 256^2 Euler).
 constexpr int kWelfordDepth = 8;
 
-template <int NF, int KIND, bool SHARE>
+template <int NF, int KIND>
 __global__ void __launch_bounds__(512)
 welford_kernel(const double* __restrict__ state, int64_t cells, int32_t batch, int64_t count0,
-               double* __restrict__ mean, double* __restrict__ m2, double* __restrict__ qout)
+               double* __restrict__ mean, double* __restrict__ m2)
 {
-    static_assert(!SHARE || KIND != 0, "only quantities divided by field 0 share it");
+    constexpr bool SHARE = KIND != 0;
     constexpr int D = kWelfordDepth;
     __shared__ double f0[SHARE ? 2 * D * 64 : 1];   // [group parity][sample][cell]
     const int q = threadIdx.x >> 6;   // the wavefront's quantity
@@ -39,25 +37,19 @@ welford_kernel(const double* __restrict__ state, int64_t cells, int32_t batch, i
     const bool live = c < cells;      // lanes past the last cell only take part in barriers
     if (!SHARE && !live) return;      // no barrier without SHARE: such lanes leave at once
     constexpr int DIV_END = (KIND == 1) ? NF - 1 : ((KIND == 3) ? 4 : NF);
-    const bool div = KIND != 0 && q >= 1 && q < DIV_END;   // uniform across the wavefront
+    const bool div = SHARE && q >= 1 && q < DIV_END;   // uniform across the wavefront
     const int64_t per = (int64_t)NF * cells;
     const double* F = state + q * cells + (live ? c : 0);
-    const double* R = state + (live ? c : 0);
-    constexpr bool LOADR = KIND != 0 && !SHARE;   // dividing wavefronts load field 0 themselves
     double mu = live ? mean[q * cells + c] : 0.0, s2 = live ? m2[q * cells + c] : 0.0;
-    double xc[D], rc[LOADR ? D : 1];
+    double xc[D];
 #pragma unroll
-    for (int i = 0; i < D; ++i) {
-        xc[i] = (live && i < batch) ? F[i * per] : 0.0;
-        if constexpr (LOADR) rc[i] = (div && live && i < batch) ? R[i * per] : 1.0;
-    }
+    for (int i = 0; i < D; ++i) xc[i] = (live && i < batch) ? F[i * per] : 0.0;
     for (int32_t b0 = 0, g = 0; b0 < batch; b0 += D, ++g) {
-        double xn[D], rn[LOADR ? D : 1];
+        double xn[D];
 #pragma unroll
         for (int i = 0; i < D; ++i) {   // the next group's loads, before this group's work
             const int32_t b = b0 + D + i;
             xn[i] = (live && b < batch) ? F[b * per] : 0.0;
-            if constexpr (LOADR) rn[i] = (div && live && b < batch) ? R[b * per] : 1.0;
         }
         double* sh = f0 + (SHARE ? (g & 1) * D * 64 : 0);
         if constexpr (SHARE) {
@@ -75,10 +67,7 @@ welford_kernel(const double* __restrict__ state, int64_t cells, int32_t batch, i
                 double x = xc[i];
                 if constexpr (SHARE) {
                     if (div) x = xc[i] * (1.0 / sh[i * 64 + lane]);
-                } else if constexpr (LOADR) {
-                    if (div) x = xc[i] * (1.0 / rc[i]);
                 }
-                if (qout) qout[b * per + q * cells + c] = x;
                 const double n = (double)(count0 + b + 1);
                 const double delta = x - mu;
                 mu = mu + (delta / n);
@@ -86,10 +75,7 @@ welford_kernel(const double* __restrict__ state, int64_t cells, int32_t batch, i
             }
         }
 #pragma unroll
-        for (int i = 0; i < D; ++i) {
-            xc[i] = xn[i];
-            if constexpr (LOADR) rc[i] = rn[i];
-        }
+        for (int i = 0; i < D; ++i) xc[i] = xn[i];
     }
     if (live) {
         mean[q * cells + c] = mu;
@@ -97,385 +83,413 @@ welford_kernel(const double* __restrict__ state, int64_t cells, int32_t batch, i
     }
 }
 
-// Structure-function partial sums. Every line of cells along every axis is cut into segments
-// of kSfSeg cells; a thread takes kSfSegsPerThread segments and accumulates, kSfLag lags at a
-// time, sum_cells (q(x + h e) - q(x))^2 over their cells: the segment's values and the window
-// q(x0 + h0 .. x0 + h0 + kSfSeg + kSfLag - 2) are loaded first (no load waits on arithmetic),
-// then the kSfSeg x kSfLag terms run with compile-time indices. Segments along y and z are
-// dealt so that neighbouring lanes take neighbouring lines (coalesced loads); along x,
-// neighbouring lanes take neighbouring segments of a row. The chunk's lags are summed over
-// the workgroup in a fixed order through LDS (per lag: 16 runs of 16 threads, then the 16
-// run sums) into one partial per workgroup. Grid: (workgroups per field, quantity, sample).
-constexpr int kSfSeg = 16;
-constexpr int kSfLag = 16;
-constexpr int kSfWin = kSfSeg + kSfLag - 1;
-constexpr int kSfThreads = 256;
-constexpr int kSfSegsPerThread = 2;
-constexpr int kSfRowLoads = (40 * 1024 / 8 + kSfThreads - 1) / kSfThreads;   // 20
+// Structure-function partial sums: for every lag h, sum (q(y) - q(y - h))^2 over the cells y of a
+// segment of a line (with the line's periodic continuation, sum over its cells of
+// (q(y + h) - q(y))^2 in another order).
+//
+// A lane takes a segment of a line and marches along it with the last W values in a ring of
+// registers (its indices are compile-time: the march is unrolled by W), so a value is read once
+// and serves W terms, a subtraction and a fused multiply-add each, into W accumulators. With more
+// than 32 lags, `split` neighbouring lanes share a segment (MULTI): each takes W lags, and a value
+// that leaves a lane's ring enters the next lane's. Neighbouring segments are the same part of
+// neighbouring lines, then the next part, so wavefronts are full also where lines are few. The sums
+// meet once, at the end. A workgroup is one wavefront (3 to a SIMD at W = 32; with four to a group,
+// whose place is free only when the last ends, 556 us against 512).
+//
+// Lines along y and z: loads four steps ahead. Lines along x: chunks of 8 columns of the
+// wavefront's segments go through LDS (8 lanes a row of 64 bytes), half a chunk ahead.
+//
+// The bound is partly memory (read once per axis, 537 MB for 256 samples of 256^2 Euler, 4.6 TB/s
+// with 8 lags) and partly FP64 issue (64 instructions per value and lane at W = 32, 120 us). The
+// kernels before this staged lines in LDS, read 47 values from there for 256 terms and summed every
+// 16 lags over the workgroup after 256 terms per thread: 322 and 296 us for the rows and the columns
+// of those samples with 32 lags, now 253 and 236.
+//
+// Beyond 64 x 32 lags a pass is repeated with the rings delayed by h0 - 1 cells, which takes a
+// second stream of the line's values (DELAY).
+constexpr int kSfBatch = 4;    // march steps between requests
+constexpr int kSfChunk = 8;    // columns staged at a time (lines along x)
+constexpr int kSfPitch = kSfChunk + 1;
+constexpr int kSfAlone = 48;   // lags of a lane that has a segment to itself
 
-struct SfGeom {
-    int32_t n[3];          // grid
-    int32_t dim;
-    int64_t lines[3];      // lines along axis d: cells / n[d]
-    int64_t segs[3];       // segments per line along axis d
-    int64_t items[4];      // first segment of axis d (items[dim] = total)
+struct SfPlan {
+    int32_t width, split;         // lags of a lane, lanes of a segment
+    int32_t seg[3];               // per axis: cells of a segment
+    int64_t segs[3];              // segments of all lines
+    int64_t first[4];             // first unit (wavefront) of each axis; first[dim..3]: their number
 };
 
-// Segments of the axes first..dim-1 (the x axis may be taken by the row kernel below).
-static SfGeom sf_geom(int32_t dim, const int32_t n[3], int first)
+// Widths 8 to 48 in one lane (37 lags of 64 samples of 256^2: 158 us per pass with one lane of 40, 2
+// wavefronts to a SIMD, 225 with two lanes of 24; 64 lags of 16 samples of 512^2: 295 with one lane
+// of 64, 275 with two of 32), else 2 to 64 lanes of 24 or 32. Segments of up to 128 cells (497 us
+// per pass of 256 samples of 256^2 with 32 lags, against 508 with 64: every segment reads W cells
+// ahead of it, and waits for them), longer ones with many lanes, which keeps the number of partial
+// sums within a small multiple of the field; shorter ones, down to 16, on grids that would have
+// fewer than 16 units. A choice by grid and lags alone: sums do not depend on the batch.
+static SfPlan sf_plan(int32_t dim, const int32_t n[3], int32_t max_h)
 {
-    SfGeom g{};
-    g.dim = dim;
+    SfPlan p{};
+    p.split = 1;
+    if (max_h > kSfAlone)
+        while (p.split < 64 && 32 * p.split < max_h) p.split *= 2;
+    const int32_t w = (max_h + 8 * p.split - 1) / (8 * p.split) * 8, most = p.split > 1 ? 32 : kSfAlone;
+    p.width = w < most ? w : most;
     const int64_t cells = (int64_t)n[0] * n[1] * n[2];
-    int64_t acc = 0;
-    for (int d = 0; d < 3; ++d) {
-        g.n[d] = n[d];
-        g.lines[d] = cells / n[d];
-        g.segs[d] = (n[d] + kSfSeg - 1) / kSfSeg;
-        g.items[d] = acc;
-        if (d >= first && d < dim) acc += g.lines[d] * g.segs[d];
+    for (int32_t len = 64 * std::max(2, p.split);; len /= 2) {
+        int64_t at = 0;
+        for (int d = 0; d < 3; ++d) {
+            const int32_t per = (n[d] + len - 1) / len;
+            p.seg[d] = (n[d] + per - 1) / per;
+            p.segs[d] = cells / n[d] * ((n[d] + p.seg[d] - 1) / p.seg[d]);
+            p.first[d] = at;
+            if (d < dim) at += (p.segs[d] * p.split + 63) / 64;
+        }
+        p.first[3] = at;
+        if (at >= 16 || len == 16) return p;
     }
-    g.items[dim] = acc;
-    for (int d = dim + 1; d < 4; ++d) g.items[d] = acc;
-    return g;
 }
 
-// Segment `item`: first cell base + x0 * stride along a line of nd cells, len cells in it.
-struct SfSeg {
-    int64_t base, stride;
-    int32_t x0, nd, len;
+struct SfArgs {
+    const double* state;   // [batch][nq][cells]
+    int32_t n[3];
+    int64_t cells;
+    int32_t axis, nq, max_h, h0;
+    int32_t seg, lsplit;   // log2 of the lanes of a segment
+    int64_t segs;          // segments of the axis
+    int64_t first, nblk;   // the axis's first unit; units of a field
+    int32_t div_lo, div_hi;
+    double* partial;       // [batch][nq][max_h][nblk]
 };
 
-__device__ __forceinline__ SfSeg sf_segment(const SfGeom& geo, int64_t item)
-{
-    SfSeg sg;
-    if (item >= geo.items[geo.dim]) {   // no segment: nothing is read or added
-        sg.base = 0; sg.stride = 1; sg.x0 = 0; sg.nd = 1; sg.len = 0;
-        return sg;
+// A line along y or z: a stream of its values from some position on, four steps ahead.
+struct SfColumn {
+    const double* q;       // the field
+    const double* rho;     // field 0
+    int32_t stride, span;  // of a line, in cells (cells < 2^31)
+    uint32_t at, end;      // the lane's next cell to request; the cell past its line
+    bool div;
+    double v[kSfBatch], r[kSfBatch], cur[kSfBatch];
+
+    template <int G>
+    __device__ __forceinline__ void load(double (&x)[G], double (&y)[G])
+    {
+        uint32_t p[G];
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            p[i] = at;
+            x[i] = q[at];
+            at += stride;
+            at = (at == end) ? at - span : at;
+        }
+        if (div) {
+#pragma unroll
+            for (int i = 0; i < G; ++i) y[i] = rho[p[i]];
+        }
     }
-    int d = 0;
-    if (item >= geo.items[1]) d = 1;
-    if (item >= geo.items[2]) d = 2;
-    const int64_t local = item - geo.items[d];
-    sg.nd = geo.n[d];
-    if (d == 0) {   // lanes along a row: item = line * segs + segment
-        const int64_t line = local / geo.segs[0];
-        sg.x0 = (int32_t)(local % geo.segs[0]) * kSfSeg;
-        sg.base = line * geo.n[0];
-        sg.stride = 1;
-    } else {        // lanes across lines: item = segment * lines + line
-        const int64_t line = local % geo.lines[d];
-        sg.x0 = (int32_t)(local / geo.lines[d]) * kSfSeg;
-        if (d == 1) {
-            const int64_t xi = line % geo.n[0], zi = line / geo.n[0];
-            sg.base = zi * geo.n[0] * geo.n[1] + xi;
-            sg.stride = geo.n[0];
+    template <int G>
+    __device__ __forceinline__ void finish(double (&out)[G], const double (&x)[G], const double (&y)[G])
+    {
+        if (div) {
+#pragma unroll
+            for (int i = 0; i < G; ++i) out[i] = x[i] * (1.0 / y[i]);
         } else {
-            sg.base = line;
-            sg.stride = (int64_t)geo.n[0] * geo.n[1];
+#pragma unroll
+            for (int i = 0; i < G; ++i) out[i] = x[i];
         }
     }
-    sg.len = (sg.nd - sg.x0 < kSfSeg) ? sg.nd - sg.x0 : kSfSeg;
-    return sg;
-}
-
-// The workgroup's sums of the chunk's kSfLag lags, stored as partial number blk_index of lag
-// h0 + l of the field whose partials start at out (out[(h - 1) * nblk + blk]). Fixed order:
-// within a wavefront a transposing butterfly over lane bits 5, 4, 3, 2 halves the lags a lane
-// holds at each step (the lane keeps the half its bit selects and adds the partner's copy of
-// it), so that lane i then holds lag i / 4 summed over 16 lanes; bits 1 and 0 finish the sums.
-// The wavefronts' sums meet in LDS (wsum[2][waves][kSfLag], alternate halves on alternate
-// chunks, so one barrier per chunk suffices) and are added in wavefront order.
-static_assert(kSfLag == 16 && kSfThreads % 64 == 0, "four halving steps over lane bits 5..2");
-constexpr int kSfWaves = kSfThreads / 64;
-
-__device__ __forceinline__ void sf_block_store(const double (&acc)[kSfLag], double* wsum,
-                                               int chunk, int h0, int max_h, double* out,
-                                               int64_t nblk, int64_t blk_index)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    double v8[8], v4[4], v2[2];
-    const bool b5 = lane & 32, b4 = lane & 16, b3 = lane & 8, b2 = lane & 4;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const double keep = b5 ? acc[8 + k] : acc[k];
-        const double give = b5 ? acc[k] : acc[8 + k];
-        v8[k] = keep + __shfl_xor(give, 32);
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const double keep = b4 ? v8[4 + k] : v8[k];
-        const double give = b4 ? v8[k] : v8[4 + k];
-        v4[k] = keep + __shfl_xor(give, 16);
-    }
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const double keep = b3 ? v4[2 + k] : v4[k];
-        const double give = b3 ? v4[k] : v4[2 + k];
-        v2[k] = keep + __shfl_xor(give, 8);
-    }
-    double v = (b2 ? v2[1] : v2[0]) + __shfl_xor(b2 ? v2[0] : v2[1], 4);
-    v = v + __shfl_xor(v, 2);     // a + b and b + a are the same double
-    v = v + __shfl_xor(v, 1);
-    double* ws = wsum + (chunk & 1) * (kSfWaves * kSfLag);
-    if ((lane & 3) == 0) ws[wave * kSfLag + (lane >> 2)] = v;
-    __syncthreads();
-    const int h = h0 + (int)threadIdx.x;
-    if (threadIdx.x < kSfLag && h <= max_h) {
-        double t = ws[threadIdx.x];
-#pragma unroll
-        for (int w = 1; w < kSfWaves; ++w) t = t + ws[w * kSfLag + threadIdx.x];
-        out[(int64_t)(h - 1) * nblk + blk_index] = t;
-    }
-}
-
-// The sums along the lines of one segment: acc[l] += sum_{r < len} (w[r + l] - v0[r])^2, each
-// lag's terms in cell order.
-__device__ __forceinline__ void sf_segment_terms(const double (&v0)[kSfSeg],
-                                                 const double (&w)[kSfWin], int len,
-                                                 double (&acc)[kSfLag])
-{
-#pragma unroll
-    for (int r = 0; r < kSfSeg; ++r) {
-        if (r < len) {
-#pragma unroll
-            for (int l = 0; l < kSfLag; ++l) {
-                const double df = w[r + l] - v0[r];
-                acc[l] = __builtin_fma(df, df, acc[l]);
-            }
-        }
-    }
-}
-
-// Lines along y and z (and x when its rows do not fit the row kernel): segments read from
-// memory, neighbouring lanes on neighbouring lines (coalesced). Partials blk_off + blk.
-__global__ void __launch_bounds__(kSfThreads)
-sf_partial_kernel(const double* __restrict__ q, const SfGeom geo, int32_t nq, int32_t max_h,
-                  int32_t nblk, int32_t blk_off, double* __restrict__ partial)
-{
-    __shared__ double wsum[2 * kSfWaves * kSfLag];
-    const int64_t cells = (int64_t)geo.n[0] * geo.n[1] * geo.n[2];
-    const int blk = blockIdx.x, qi = blockIdx.y, b = blockIdx.z;
-    const double* Q = q + ((int64_t)b * nq + qi) * cells;
-    double* out = partial + ((int64_t)b * nq + qi) * max_h * nblk;
-    const int64_t item0 = (int64_t)blk * kSfThreads * kSfSegsPerThread + threadIdx.x;
-
-    for (int h0 = 1, ch = 0; h0 <= max_h; h0 += kSfLag, ++ch) {
-        // lags past max_h are summed as well and never stored (their window stays in the line)
-        double acc[kSfLag];
-#pragma unroll
-        for (int l = 0; l < kSfLag; ++l) acc[l] = 0.0;
-#pragma unroll 1   // one segment's values in registers at a time (3 wavefronts per SIMD)
-        for (int j = 0; j < kSfSegsPerThread; ++j) {
-            const SfSeg sg = sf_segment(geo, item0 + (int64_t)j * kSfThreads);
-            if (sg.len == 0) continue;
-            // 32-bit cell indices (a field has < 2^31 cells) off the workgroup's field base
-            const uint32_t base = (uint32_t)sg.base, stride = (uint32_t)sg.stride;
-            double v0[kSfSeg], w[kSfWin];
-#pragma unroll
-            for (int r = 0; r < kSfSeg; ++r)   // positions past a ragged line's end are skipped
-                v0[r] = Q[base + (uint32_t)(r < sg.len ? sg.x0 + r : sg.x0) * stride];
-            uint32_t p = (uint32_t)((sg.x0 + h0) % sg.nd);
-#pragma unroll
-            for (int k = 0; k < kSfWin; ++k) {
-                w[k] = Q[base + p * stride];
-                p = (p + 1 == (uint32_t)sg.nd) ? 0u : p + 1;
-            }
-            sf_segment_terms(v0, w, sg.len, acc);
-        }
-        sf_block_store(acc, wsum, ch, h0, max_h, out, nblk, blk_off + blk);
-    }
-}
-
-// Staged lines. A workgroup takes 16 lines and 16 consecutive segments of each (256 cells),
-// and stages those cells plus the cells their lag windows reach (the periodic continuation,
-// so no wrap remains) in LDS with loads issued all at once; every thread then takes one
-// (line, segment) and reads its values and windows from LDS at fixed offsets. Lags up to
-// kSfStripLags (larger max_h: sf_partial_kernel).
-constexpr int kSfStripLines = 16;
-constexpr int kSfStripSegs = 16;
-constexpr int kSfStripSpan = kSfStripSegs * kSfSeg;                   // 256 cells per line
-constexpr int kSfStripLags = 64;
-constexpr int kSfStripExt = kSfStripSpan + kSfStripLags + kSfSeg;     // cells staged per line
-static_assert(kSfStripLines * kSfStripSegs == kSfThreads, "one (line, segment) per thread");
-
-// Lines along y or z: 16 lines adjacent in memory (consecutive x), stride S between a line's
-// cells; tile[e][c] = cell e of line c (lanes on neighbouring lines read neighbouring slots).
-// Blocks: (strip of 16 x, other coordinate, group of 16 segments); partials blk_off + blk.
-__global__ void __launch_bounds__(kSfThreads)
-sf_cols_kernel(const double* __restrict__ q, int32_t nx, int32_t L, int64_t S, int64_t other_stride,
-               int32_t strips_x, int32_t nother, int32_t groups, int32_t nq, int32_t max_h,
-               int32_t nblk, int32_t blk_off, int64_t cells, int32_t div_lo, int32_t div_hi,
-               double* __restrict__ partial)
-{
-    __shared__ double tile[kSfStripExt * kSfStripLines];
-    __shared__ double wsum[2 * kSfWaves * kSfLag];
-    const int blk = blockIdx.x, qi = blockIdx.y, b = blockIdx.z;
-    const int g = blk % groups, rest = blk / groups;
-    const int sx = rest % strips_x, o = rest / strips_x;
-    const int x0 = sx * kSfStripLines;
-    const int32_t P0 = g * kSfStripSpan;                      // first cell of the group
-    const int segs = (L + kSfSeg - 1) / kSfSeg;
-    const int chunks = (max_h + kSfLag - 1) / kSfLag;
-    const int ext = min(kSfStripExt, kSfStripSpan + chunks * kSfLag + kSfSeg);
-    const double* Q = q + ((int64_t)b * nq + qi) * cells + (int64_t)o * other_stride + x0;
-    const double* R = q + (int64_t)b * nq * cells + (int64_t)o * other_stride + x0;   // field 0
-    const bool div = qi >= div_lo && qi < div_hi;   // uniform over the workgroup
-    double* out = partial + ((int64_t)b * nq + qi) * max_h * nblk;
+    template <int G>
+    __device__ __forceinline__ void fetch(double* out, double*)   // G values at once
     {
-        constexpr int NL = kSfStripExt * kSfStripLines / kSfThreads;
-        double v[NL], r[NL];
-        const int c = threadIdx.x & (kSfStripLines - 1);
-        const bool col_ok = x0 + c < nx;
+        double x[G], y[G], z[G];
+        load<G>(x, y);
+        finish<G>(z, x, y);
 #pragma unroll
-        for (int k = 0; k < NL; ++k) {
-            const int e = (threadIdx.x >> 4) + k * (kSfThreads / kSfStripLines);
-            r[k] = 1.0;
-            if (e < ext && col_ok) {
-                int32_t p = P0 + e;
-                p = (p < L) ? p : p - L;
-                if (p >= L) p %= L;
-                v[k] = Q[(int64_t)p * S + c];
-                if (div) r[k] = R[(int64_t)p * S + c];
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < NL; ++k) {
-            const int e = (threadIdx.x >> 4) + k * (kSfThreads / kSfStripLines);
-            if (e < ext && col_ok) tile[e * kSfStripLines + c] = div ? v[k] * (1.0 / r[k]) : v[k];
-        }
+        for (int i = 0; i < G; ++i) out[i] = z[i];
     }
-    __syncthreads();
-    const int c = threadIdx.x & (kSfStripLines - 1), sl = threadIdx.x >> 4;
-    const int sgi = g * kSfStripSegs + sl;
-    const bool ok = sgi < segs && x0 + c < nx;
-    const int len = ok ? min(kSfSeg, L - sgi * kSfSeg) : 0;
-    const double* T = tile + sl * kSfSeg * kSfStripLines + c;
-    for (int h0 = 1, ch = 0; h0 <= max_h; h0 += kSfLag, ++ch) {
-        double acc[kSfLag];
-#pragma unroll
-        for (int l = 0; l < kSfLag; ++l) acc[l] = 0.0;
-        if (ok) {
-            double v0[kSfSeg], w[kSfWin];
-#pragma unroll
-            for (int i = 0; i < kSfSeg; ++i) v0[i] = T[i * kSfStripLines];
-            const double* W = T + h0 * kSfStripLines;
-#pragma unroll
-            for (int k = 0; k < kSfWin; ++k) w[k] = W[k * kSfStripLines];
-            sf_segment_terms(v0, w, len, acc);
-        }
-        sf_block_store(acc, wsum, ch, h0, max_h, out, nblk, blk_off + blk);
-    }
-}
-
-// Lines along x (rows): 16 rows, each staged with element e at e + e / 16, so that the 16
-// segments of a row, which neighbouring lanes take, start 17 slots apart (different banks).
-// Blocks: (group of 16 rows, group of 16 segments); partials blk_off + blk.
-constexpr int kSfRowPitch = kSfStripExt + kSfStripExt / 16 + 1;
-
-__global__ void __launch_bounds__(kSfThreads)
-sf_rows_kernel(const double* __restrict__ q, int32_t L, int64_t rows, int32_t groups, int32_t nq,
-               int32_t max_h, int32_t nblk, int32_t blk_off, int32_t div_lo, int32_t div_hi,
-               double* __restrict__ partial)
-{
-    __shared__ double tile[kSfStripLines * kSfRowPitch];
-    __shared__ double wsum[2 * kSfWaves * kSfLag];
-    const int blk = blockIdx.x, qi = blockIdx.y, b = blockIdx.z;
-    const int g = blk % groups;
-    const int64_t row0 = (int64_t)(blk / groups) * kSfStripLines;
-    const int32_t P0 = g * kSfStripSpan;
-    const int segs = (L + kSfSeg - 1) / kSfSeg;
-    const int chunks = (max_h + kSfLag - 1) / kSfLag;
-    const int ext = min(kSfStripExt, kSfStripSpan + chunks * kSfLag + kSfSeg);
-    const int64_t cells = rows * L;
-    const double* Q = q + ((int64_t)b * nq + qi) * cells;
-    const double* R0 = q + (int64_t)b * nq * cells;   // field 0 of the sample
-    const bool div = qi >= div_lo && qi < div_hi;     // uniform over the workgroup
-    double* out = partial + ((int64_t)b * nq + qi) * max_h * nblk;
+    __device__ __forceinline__ void begin(double*) { fetch<kSfBatch>(cur, nullptr); }
+    __device__ __forceinline__ void request() { load<kSfBatch>(v, r); }
+    __device__ __forceinline__ void take(double (&out)[kSfBatch], double*)
     {
-        constexpr int PER = (kSfStripExt + kSfThreads - 1) / kSfThreads;   // loads per row
-        double v[kSfStripLines][PER], d[kSfStripLines][PER];
 #pragma unroll
-        for (int r = 0; r < kSfStripLines; ++r)
-#pragma unroll
-            for (int j = 0; j < PER; ++j) {
-                const int e = threadIdx.x + j * kSfThreads;
-                d[r][j] = 1.0;
-                if (e < ext && row0 + r < rows) {
-                    int32_t p = P0 + e;
-                    p = (p < L) ? p : p - L;
-                    if (p >= L) p %= L;
-                    v[r][j] = Q[(row0 + r) * L + p];
-                    if (div) d[r][j] = R0[(row0 + r) * L + p];
-                }
-            }
-#pragma unroll
-        for (int r = 0; r < kSfStripLines; ++r)
-#pragma unroll
-            for (int j = 0; j < PER; ++j) {
-                const int e = threadIdx.x + j * kSfThreads;
-                if (e < ext && row0 + r < rows)
-                    tile[r * kSfRowPitch + e + (e >> 4)] = div ? v[r][j] * (1.0 / d[r][j]) : v[r][j];
-            }
+        for (int i = 0; i < kSfBatch; ++i) out[i] = cur[i];
     }
-    __syncthreads();
-    const int sl = threadIdx.x & (kSfStripSegs - 1), r = threadIdx.x >> 4;
-    const int sgi = g * kSfStripSegs + sl;
-    const bool ok = sgi < segs && row0 + r < rows;
-    const int len = ok ? min(kSfSeg, L - sgi * kSfSeg) : 0;
-    const double* T = tile + r * kSfRowPitch + 17 * sl;   // element 16 sl of the row
-    for (int h0 = 1, c = 0; h0 <= max_h; h0 += kSfLag, ++c) {
-        double acc[kSfLag];
-#pragma unroll
-        for (int l = 0; l < kSfLag; ++l) acc[l] = 0.0;
-        if (ok) {
-            // element 16 sl + m is at T[m + (m >> 4)]; for m = h0 + k, h0 = 1 + 16 c:
-            // (m >> 4) = c + ((1 + k) >> 4)
-            const double* W = T + h0 + c;
-            double v0[kSfSeg], w[kSfWin];
-#pragma unroll
-            for (int i = 0; i < kSfSeg; ++i) v0[i] = T[i];
-#pragma unroll
-            for (int k = 0; k < kSfWin; ++k) w[k] = W[k + ((1 + k) >> 4)];
-            sf_segment_terms(v0, w, len, acc);
-        }
-        sf_block_store(acc, wsum, c, h0, max_h, out, nblk, blk_off + blk);
-    }
-}
-
-// The staged kernels' blocks per field: rows, then y columns, then z columns (0 when max_h
-// exceeds the staged lags: the general kernel takes every axis then).
-struct SfStripPlan {
-    bool use;
-    int64_t rows_blocks, col_blocks[3];
-    int32_t groups[3], strips_x;
+    __device__ __forceinline__ void commit(double*) { finish<kSfBatch>(cur, v, r); }
 };
 
-static SfStripPlan sf_strip_plan(int32_t dim, const int32_t n[3], int32_t max_h)
+// The same for lines along x, through LDS (buf: two chunks of 64 segments x kSfPitch).
+struct SfRow {
+    const double* q;       // the field
+    const double* rho;
+    const int2* seg;       // per segment of the wavefront: first cell of its line, first column
+    int32_t n, y;          // cells of a line; next chunk's distance from the segment's first, mod n
+    bool div;
+    int32_t half, side;    // half of the chunk at hand; buffer it is in
+    double v[kSfBatch], r[kSfBatch];
+
+    static __device__ __forceinline__ int32_t slot(int k) { return k * 8 + ((threadIdx.x & 63) >> 3); }
+
+    // The values of segments slot(k0), slot(k0 + 1), ... of the next chunk.
+    template <int G>
+    __device__ __forceinline__ void load(double* x, double* y, int k0)
+    {
+        const int j = threadIdx.x & (kSfChunk - 1);
+        int32_t c[G];
+#pragma unroll
+        for (int t = 0; t < G; ++t) {
+            const int2 g = seg[slot(k0 + t)];
+            uint32_t p = (uint32_t)g.y + (uint32_t)(this->y + j);   // below 2 n + 6
+            p = p < (uint32_t)n ? p : p - n;
+            p = p < (uint32_t)n ? p : p - n;
+            if (n < kSfChunk) p %= (uint32_t)n;   // uniform
+            c[t] = g.x + (int32_t)p;              // cells < 2^31
+            x[t] = q[c[t]];
+        }
+        if (div) {
+#pragma unroll
+            for (int t = 0; t < G; ++t) y[t] = rho[c[t]];
+        }
+    }
+    template <int G>
+    __device__ __forceinline__ void store(const double* x, const double* y, double* buf, int k0)
+    {
+        double* p = buf + slot(k0) * kSfPitch + (threadIdx.x & (kSfChunk - 1));
+        if (div) {
+#pragma unroll
+            for (int t = 0; t < G; ++t) p[t * 8 * kSfPitch] = x[t] * (1.0 / y[t]);
+        } else {
+#pragma unroll
+            for (int t = 0; t < G; ++t) p[t * 8 * kSfPitch] = x[t];
+        }
+    }
+    __device__ __forceinline__ void advance()
+    {
+        y += kSfChunk;
+        if (y >= n) y = (y - n) % n;
+    }
+    template <int G>
+    __device__ __forceinline__ void fetch(double* out, double* buf)   // G = 8 or 16 values at once
+    {
+        constexpr int C = G / kSfChunk;   // chunks
+        double x[C][8], z[C][8];
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            load<8>(x[c], z[c], 0);
+            advance();
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c) store<8>(x[c], z[c], buf + c * 64 * kSfPitch, 0);
+        wave_fence();
+#pragma unroll
+        for (int i = 0; i < G; ++i)
+            out[i] = buf[((i / kSfChunk) * 64 + (threadIdx.x & 63)) * kSfPitch + i % kSfChunk];
+        wave_fence();
+    }
+    __device__ __forceinline__ void begin(double* buf)
+    {
+        double x[8], z[8];
+        load<8>(x, z, 0);
+        advance();
+        store<8>(x, z, buf, 0);
+        wave_fence();
+        half = side = 0;
+    }
+    __device__ __forceinline__ void request() { load<kSfBatch>(v, r, half * kSfBatch); }
+    __device__ __forceinline__ void take(double (&out)[kSfBatch], double* buf)
+    {
+        const double* p = buf + (side * 64 + (threadIdx.x & 63)) * kSfPitch + half * kSfBatch;
+#pragma unroll
+        for (int i = 0; i < kSfBatch; ++i) out[i] = p[i];
+    }
+    __device__ __forceinline__ void commit(double* buf)
+    {
+        store<kSfBatch>(v, r, buf + (side ^ 1) * 64 * kSfPitch, half * kSfBatch);
+        half ^= 1;
+        if (half == 0) {
+            side ^= 1;
+            advance();
+            wave_fence();
+        }
+    }
+};
+
+// The W cells ahead of a segment.
+template <int W, class Line>
+__device__ __forceinline__ void sf_fill(Line& line, double (&ring)[W], double* buf)
 {
-    SfStripPlan p{};
-    p.use = max_h <= kSfStripLags;
-    if (!p.use) return p;
-    for (int d = 0; d < dim; ++d) p.groups[d] = ((n[d] + kSfSeg - 1) / kSfSeg + kSfStripSegs - 1) / kSfStripSegs;
-    const int64_t rows = (int64_t)n[1] * n[2];
-    p.rows_blocks = (rows + kSfStripLines - 1) / kSfStripLines * p.groups[0];
-    p.strips_x = (n[0] + kSfStripLines - 1) / kSfStripLines;
-    if (dim >= 2) p.col_blocks[1] = (int64_t)p.strips_x * n[2] * p.groups[1];
-    if (dim >= 3) p.col_blocks[2] = (int64_t)p.strips_x * n[1] * p.groups[2];
-    return p;
+#pragma unroll
+    for (int s0 = 0; s0 + 16 <= W; s0 += 16) line.template fetch<16>(ring + s0, buf);
+    if constexpr (W % 16 != 0) line.template fetch<8>(ring + W / 16 * 16, buf);
 }
 
-// S_q(h) of every sample of the chunk: the workgroup partials of (sample, quantity, lag)
-// summed in workgroup order and normalised. One thread per (sample, quantity, lag).
-__global__ void sf_sum_kernel(const double* __restrict__ partial, int32_t n_out, int32_t nblk,
+// Sums over the wavefront of W accumulators per lane, in a fixed order: a transposing butterfly
+// halves the lags that a lane holds at each step (the lane keeps the half that its bit selects and
+// adds the partner's copy of it); the remaining steps finish the sums. The sum of lag h0 + l ends
+// in the lanes l * 64 / W and following.
+template <int H, int M, int W>
+__device__ __forceinline__ void sf_wave_sum(double (&v)[W])
+{
+    if constexpr (H >= 1) {
+        const bool up = threadIdx.x & M;
+#pragma unroll
+        for (int k = 0; k < H; ++k) {
+            const double keep = up ? v[H + k] : v[k];
+            const double give = up ? v[k] : v[H + k];
+            v[k] = keep + __shfl_xor(give, M);
+        }
+        sf_wave_sum<H / 2, M / 2>(v);
+    } else if constexpr (M >= 1) {
+        v[0] = v[0] + __shfl_xor(v[0], M);
+        sf_wave_sum<0, M / 2>(v);
+    }
+}
+
+// The preceding lane's value (lane 0: unspecified).
+__device__ __forceinline__ double sf_from_left(double x)
+{
+    constexpr int WAVE_SHR1 = 0x138;
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), WAVE_SHR1, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), WAVE_SHR1, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+
+// a: the stream from the segment's first cell; d (DELAY): the same, delayed. ring: the W cells
+// ahead of them; head: first lane of a segment; len: cells of the lane's segment, most: of any.
+template <int W, bool MULTI, bool DELAY, class Line>
+__device__ __forceinline__ void sf_march(Line& a, Line& d, double* abuf, double* dbuf, bool head,
+                                         int32_t len, int32_t most, double (&ring)[W],
+                                         double (&acc)[W])
+{
+    a.begin(abuf);
+    if (DELAY) d.begin(dbuf);
+#pragma unroll 1
+    for (int32_t y = 0; y < most; y += W) {
+#pragma unroll
+        for (int s0 = 0; s0 < W; s0 += kSfBatch) {
+            if (y + s0 < most) {   // uniform
+                double v[kSfBatch], r[kSfBatch];
+                a.request();
+                if (DELAY) d.request();
+                a.take(v, abuf);
+                if (DELAY) d.take(r, dbuf);
+#pragma unroll
+                for (int i = 0; i < kSfBatch; ++i) {
+                    const int s = s0 + i;
+                    if (y + s < len) {
+#pragma unroll
+                        for (int l = 0; l < W; l += 4) {
+                            double d0 = v[i] - ring[(s - l - 1 + W) % W];
+                            double d1 = v[i] - ring[(s - l - 2 + W) % W];
+                            double d2 = v[i] - ring[(s - l - 3 + W) % W];
+                            double d3 = v[i] - ring[(s - l - 4 + W) % W];
+                            // four at a time, since a result takes two issues (beyond 32 lags the
+                            // unroller would give up)
+                            if constexpr (W <= 32)
+                                asm volatile("" : "+v"(d0), "+v"(d1), "+v"(d2), "+v"(d3));
+                            acc[l] = __builtin_fma(d0, d0, acc[l]);
+                            acc[l + 1] = __builtin_fma(d1, d1, acc[l + 1]);
+                            acc[l + 2] = __builtin_fma(d2, d2, acc[l + 2]);
+                            acc[l + 3] = __builtin_fma(d3, d3, acc[l + 3]);
+                        }
+                    }
+                    const double in = DELAY ? r[i] : v[i];
+                    if constexpr (MULTI) {
+                        const double left = sf_from_left(ring[s]);
+                        ring[s] = head ? in : left;
+                    } else ring[s] = in;
+                }
+                a.commit(abuf);
+                if (DELAY) d.commit(dbuf);
+            }
+        }
+    }
+}
+
+template <int W, bool MULTI, bool DELAY, bool ROWS>
+__global__ void __launch_bounds__(64)
+__attribute__((amdgpu_waves_per_eu(W > 48 ? 1 : (W > 32 || DELAY ? 2 : (W >= 24 ? 3 : 4)), 8)))
+sf_kernel(const SfArgs a)
+{
+    constexpr int BUF = 2 * 64 * kSfPitch;
+    __shared__ double lds[ROWS ? BUF * (DELAY ? 2 : 1) : 1];
+    __shared__ int2 seg[ROWS ? 64 : 1];
+    const int lane = threadIdx.x;
+    const int64_t unit = blockIdx.x;
+    const int lsplit = MULTI ? a.lsplit : 0, part = lane & ((1 << lsplit) - 1);
+    const int64_t want = (unit * 64 + lane) >> lsplit;
+    const bool live = want < a.segs;
+    const uint32_t at = (uint32_t)(live ? want : a.segs - 1);   // segs <= cells < 2^31
+    const int32_t n = a.n[a.axis];
+    const uint32_t lines = (uint32_t)(a.cells / n);
+    const int32_t line = (int32_t)(at % lines), y0 = (int32_t)(at / lines) * a.seg;
+    const int32_t len = !live ? 0 : (n - y0 < a.seg ? n - y0 : a.seg);
+    const int qi = blockIdx.y, b = blockIdx.z;
+    const double* F = a.state + ((int64_t)b * a.nq + qi) * a.cells;
+    const double* R = a.state + (int64_t)b * a.nq * a.cells;
+    const bool div = qi >= a.div_lo && qi < a.div_hi;
+    const int32_t shift = a.h0 - 1;
+    // first cells of the lane's ring and of the delayed stream
+    const int32_t yr = wrap_index(y0 - shift - (part + 1) * W, n, BC_PERIODIC);
+    const int32_t yd = DELAY ? wrap_index(y0 - shift, n, BC_PERIODIC) : 0;
+    double ring[W], acc[W];
+#pragma unroll
+    for (int l = 0; l < W; ++l) acc[l] = 0.0;
+    if constexpr (ROWS) {
+        double* dbuf = lds + (DELAY ? BUF : 0);
+        seg[lane] = make_int2(line * n, yr);
+        wave_fence();
+        SfRow d{F, R, seg, n, 0, div};
+        sf_fill<W>(d, ring, lds);
+        seg[lane] = make_int2(line * n, y0);
+        wave_fence();
+        SfRow v{F, R, seg, n, 0, div};
+        if (DELAY) d = SfRow{F, R, seg, n, n - shift % n, div};
+        if (DELAY && d.y == n) d.y = 0;
+        sf_march<W, MULTI, DELAY>(v, d, lds, dbuf, part == 0, len, a.seg, ring, acc);
+    } else {
+        const int32_t stride = (a.axis == 1) ? a.n[0] : a.n[0] * a.n[1];
+        const uint32_t base = (uint32_t)(line / stride) * stride * n + line % stride;
+        const uint32_t end = base + n * stride;   // < 2^32: base and span are below 2^31
+        SfColumn v{F, R, stride, n * stride, base + yr * stride, end, div};
+        sf_fill<W>(v, ring, nullptr);
+        v.at = base + y0 * stride;
+        SfColumn d{F, R, stride, n * stride, base + yd * stride, end, div};
+        sf_march<W, MULTI, DELAY>(v, d, nullptr, nullptr, part == 0, len, a.seg, ring, acc);
+    }
+    double* out = a.partial + ((int64_t)b * a.nq + qi) * a.max_h * a.nblk + a.first + unit;
+    if constexpr (MULTI) {   // lanes of one part of the lags are 1 << lsplit apart
+#pragma unroll
+        for (int l = 0; l < W; ++l) {
+            for (int m = 32; m >= 1 << lsplit; m /= 2) acc[l] = acc[l] + __shfl_xor(acc[l], m);
+            const int h = a.h0 + part * W + l;
+            if (lane == part && h <= a.max_h) out[(int64_t)(h - 1) * a.nblk] = acc[l];
+        }
+    } else {
+        constexpr int P = W <= 8 ? 8 : (W <= 16 ? 16 : (W <= 32 ? 32 : 64));   // lags, padded
+        double sum[P];
+#pragma unroll
+        for (int l = 0; l < P; ++l) sum[l] = l < W ? acc[l] : 0.0;
+        sf_wave_sum<P / 2, 32>(sum);
+        const int l = lane / (64 / P), h = a.h0 + l;
+        if (lane % (64 / P) == 0 && l < W && h <= a.max_h) out[(int64_t)(h - 1) * a.nblk] = sum[0];
+    }
+}
+
+// S_q(h) of every sample of the chunk: the unit partials of (sample, quantity, lag) summed and
+// normalised. kSumLanes lanes per (sample, quantity, lag), each over every kSumLanes-th unit, for
+// loads in flight and in whole lines (512 x 512, 64 lags, 128 units: 5.9 us, with one lane 18.8).
+constexpr int kSumLanes = 8;
+__global__ void sf_sum_kernel(const double* __restrict__ partial, int32_t n_out, int64_t nblk,
                               double denom, double* __restrict__ x)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n_out) return;
-    const double* p = partial + (int64_t)t * nblk;
-    double s = p[0];
-    for (int k = 1; k < nblk; ++k) s = s + p[k];
-    x[t] = s / denom;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t t = i / kSumLanes;
+    const int lane = (int)(i % kSumLanes);
+    double s = 0.0;   // sums of squares: +0 is neutral
+    if (t < n_out)
+        for (int64_t k = lane; k < nblk; k += kSumLanes) s = s + partial[t * nblk + k];
+#pragma unroll
+    for (int m = kSumLanes / 2; m >= 1; m /= 2) s = s + __shfl_xor(s, m);
+    if (t < n_out && lane == 0) x[t] = s / denom;
 }
 
 // Moments over samples of S_q(h), in sample order. One thread per (quantity, lag).
@@ -632,83 +646,84 @@ __global__ void fill_zero_kernel(double* __restrict__ p, int64_t n)
         p[i] = 0.0;
 }
 
-int sf_blocks_per_field(int32_t dim, const int32_t n[3], int32_t max_h)
+int64_t sf_units(int32_t dim, const int32_t n[3], int32_t max_h)
 {
-    const SfStripPlan sp = sf_strip_plan(dim, n, max_h);
-    if (sp.use) return (int)(sp.rows_blocks + sp.col_blocks[1] + sp.col_blocks[2]);
-    const SfGeom g = sf_geom(dim, n, 0);
-    const int64_t per = (int64_t)kSfThreads * kSfSegsPerThread;
-    return (int)((g.items[dim] + per - 1) / per);
+    return sf_plan(dim, n, max_h).first[3];
 }
 
 template <int NF, int KIND>
 static void welford_launch(const double* state, int64_t cells, int32_t batch, int64_t count0,
-                           double* mean, double* m2, double* qout, hipStream_t s)
+                           double* mean, double* m2, hipStream_t s)
 {
     static_assert(NF * 64 <= 512, "one wavefront per quantity");
     const unsigned nb = (unsigned)((cells + 63) / 64);
-    constexpr bool SHARE = KIND != 0;
-    if (SHARE && !qout)
-        hipLaunchKernelGGL((welford_kernel<NF, KIND, SHARE>), dim3(nb), dim3(64 * NF), 0, s, state,
-                           cells, batch, count0, mean, m2, qout);
-    else
-        hipLaunchKernelGGL((welford_kernel<NF, KIND, false>), dim3(nb), dim3(64 * NF), 0, s, state,
-                           cells, batch, count0, mean, m2, qout);
+    hipLaunchKernelGGL((welford_kernel<NF, KIND>), dim3(nb), dim3(64 * NF), 0, s, state, cells, batch,
+                       count0, mean, m2);
 }
 
 void launch_welford(int nf, int kind, const double* state, int64_t cells, int32_t batch,
-                    int64_t count0, double* mean, double* m2, double* qout, hipStream_t s)
+                    int64_t count0, double* mean, double* m2, hipStream_t s)
 {
-    if (kind == 0) welford_launch<1, 0>(state, cells, batch, count0, mean, m2, qout, s);
-    else if (kind == 3) welford_launch<8, 3>(state, cells, batch, count0, mean, m2, qout, s);
-    else if (kind == 2 && nf == 2) welford_launch<2, 2>(state, cells, batch, count0, mean, m2, qout, s);
-    else if (kind == 2) welford_launch<3, 2>(state, cells, batch, count0, mean, m2, qout, s);
-    else if (nf == 3) welford_launch<3, 1>(state, cells, batch, count0, mean, m2, qout, s);
-    else if (nf == 4) welford_launch<4, 1>(state, cells, batch, count0, mean, m2, qout, s);
-    else welford_launch<5, 1>(state, cells, batch, count0, mean, m2, qout, s);
+    if (kind == 0) welford_launch<1, 0>(state, cells, batch, count0, mean, m2, s);
+    else if (kind == 3) welford_launch<8, 3>(state, cells, batch, count0, mean, m2, s);
+    else if (kind == 2 && nf == 2) welford_launch<2, 2>(state, cells, batch, count0, mean, m2, s);
+    else if (kind == 2) welford_launch<3, 2>(state, cells, batch, count0, mean, m2, s);
+    else if (nf == 3) welford_launch<3, 1>(state, cells, batch, count0, mean, m2, s);
+    else if (nf == 4) welford_launch<4, 1>(state, cells, batch, count0, mean, m2, s);
+    else welford_launch<5, 1>(state, cells, batch, count0, mean, m2, s);
 }
 
-bool sf_staged(int32_t max_h) { return max_h <= kSfStripLags; }
-
-void launch_sf_partial(const double* q, int32_t dim, const int32_t n[3], int32_t nq, int32_t max_h,
-                       int32_t batch, int kind, double* partial, hipStream_t s)
+template <int W, bool MULTI, bool DELAY>
+static void sf_launch(const SfArgs& a, int32_t batch, hipStream_t s)
 {
-    const int nblk = sf_blocks_per_field(dim, n, max_h);
-    const SfStripPlan sp = sf_strip_plan(dim, n, max_h);
+    const dim3 grid((unsigned)(((a.segs << a.lsplit) + 63) / 64), a.nq, batch), block(64);
+    if (a.axis == 0) hipLaunchKernelGGL((sf_kernel<W, MULTI, DELAY, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((sf_kernel<W, MULTI, DELAY, false>), grid, block, 0, s, a);
+}
+
+void launch_sf_partial(const double* state, int32_t dim, const int32_t n[3], int32_t nq,
+                       int32_t max_h, int32_t batch, int kind, double* partial, hipStream_t s)
+{
+    const SfPlan p = sf_plan(dim, n, max_h);
+    SfArgs a{};
+    a.state = state;
+    for (int d = 0; d < 3; ++d) a.n[d] = n[d];
+    a.cells = (int64_t)n[0] * n[1] * n[2];
+    a.nq = nq;
+    a.max_h = max_h;
+    a.nblk = p.first[3];
+    a.partial = partial;
+    while (1 << a.lsplit < p.split) ++a.lsplit;
     // quantities formed from the state as the Welford pass forms them: fields div_lo..div_hi-1
     // divided by field 0
-    const int32_t div_lo = kind > 0 ? 1 : 0;
-    const int32_t div_hi = kind == 1 ? nq - 1 : (kind == 3 ? 4 : (kind == 2 ? nq : 0));
-    if (!sp.use) {   // sp.use == sf_staged(max_h): here q holds the quantities (kind < 0)
-        hipLaunchKernelGGL(sf_partial_kernel, dim3(nblk, nq, batch), dim3(kSfThreads), 0, s, q,
-                           sf_geom(dim, n, 0), nq, max_h, nblk, 0, partial);
-        return;
-    }
-    const int64_t cells = (int64_t)n[0] * n[1] * n[2];
-    hipLaunchKernelGGL(sf_rows_kernel, dim3((unsigned)sp.rows_blocks, nq, batch), dim3(kSfThreads),
-                       0, s, q, n[0], (int64_t)n[1] * n[2], sp.groups[0], nq, max_h, nblk, 0,
-                       div_lo, div_hi, partial);
-    int64_t off = sp.rows_blocks;
-    for (int d = 1; d < dim; ++d) {
-        const int64_t S = (d == 1) ? n[0] : (int64_t)n[0] * n[1];
-        // the other coordinate: z for y lines (stride nx ny), y for z lines (stride nx)
-        const int64_t other_stride = (d == 1) ? (int64_t)n[0] * n[1] : n[0];
-        const int32_t nother = (d == 1) ? n[2] : n[1];
-        hipLaunchKernelGGL(sf_cols_kernel, dim3((unsigned)sp.col_blocks[d], nq, batch),
-                           dim3(kSfThreads), 0, s, q, n[0], n[d], S, other_stride, sp.strips_x,
-                           nother, sp.groups[d], nq, max_h, nblk, (int)off, cells, div_lo, div_hi,
-                           partial);
-        off += sp.col_blocks[d];
+    a.div_lo = kind > 0 ? 1 : 0;
+    a.div_hi = kind == 1 ? nq - 1 : (kind == 3 ? 4 : (kind == 2 ? nq : 0));
+    for (a.h0 = 1; a.h0 <= max_h; a.h0 += p.width * p.split) {
+        for (a.axis = 0; a.axis < dim; ++a.axis) {
+            a.seg = p.seg[a.axis];
+            a.segs = p.segs[a.axis];
+            a.first = p.first[a.axis];
+            if (a.h0 > 1) sf_launch<32, true, true>(a, batch, s);   // width 32: max_h > 64 * 32
+            else if (p.split > 1 && p.width == 24) sf_launch<24, true, false>(a, batch, s);
+            else if (p.split > 1) sf_launch<32, true, false>(a, batch, s);
+            else if (p.width == 48) sf_launch<48, false, false>(a, batch, s);
+            else if (p.width == 40) sf_launch<40, false, false>(a, batch, s);
+            else if (p.width == 32) sf_launch<32, false, false>(a, batch, s);
+            else if (p.width == 24) sf_launch<24, false, false>(a, batch, s);
+            else if (p.width == 16) sf_launch<16, false, false>(a, batch, s);
+            else sf_launch<8, false, false>(a, batch, s);
+        }
     }
 }
 
-void launch_sf_welford(const double* partial, int32_t nq, int32_t max_h, int32_t nblk,
+void launch_sf_welford(const double* partial, int32_t nq, int32_t max_h, int64_t nblk,
                        int32_t batch, int64_t count0, double denom, double* x, double* s2mean,
                        double* s2m2, hipStream_t s)
 {
     const int n_out = batch * nq * max_h;
-    hipLaunchKernelGGL(sf_sum_kernel, dim3((n_out + 255) / 256), dim3(256), 0, s, partial, n_out,
-                       nblk, denom, x);
+    const int64_t threads = (int64_t)n_out * kSumLanes;
+    hipLaunchKernelGGL(sf_sum_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, partial,
+                       n_out, nblk, denom, x);
     const int t = nq * max_h;
     hipLaunchKernelGGL(sf_welford_kernel, dim3((t + 63) / 64), dim3(64), 0, s, x, nq, max_h, batch,
                        count0, s2mean, s2m2);
