@@ -323,16 +323,24 @@ __device__ __forceinline__ int find_group(const Group* g, int ngroups, int64_t b
 
 // Fewest waves per SIMD the register allocation must leave room for: 6 for the LDS-held tile
 // plans; the Euler Godunov flux (a Newton iteration with logarithms and exponentials) needs
-// 116-148 registers and would spill under the 80 that 6 waves leave, so it is allowed 2.
-template <int EQ, int FLUX, int HOLD>
-constexpr int stage_min_waves() { return (FLUX == FLUX_GODUNOV && EQ == EQ_EULER) ? 2 : (HOLD ? 6 : 1); }
+// 116-148 registers and would spill under the 80 that 6 waves leave, so it is allowed 2; Roe's flux
+// and the short fluxes of ideal MHD's eight fields spilled 9 to 19 registers there and are allowed 5
+// (4 in 3D) and 4.
+template <int DIM, int EQ, int RECON, int FLUX, int HOLD>
+constexpr int stage_min_waves()
+{
+    if (FLUX == FLUX_GODUNOV && EQ == EQ_EULER) return 2;
+    if (!HOLD) return 1;
+    if (FLUX == FLUX_ROE) return DIM == 3 ? 4 : 5;
+    return short_flux<EQ, RECON, FLUX>() && EQ == EQ_MHD ? 4 : 6;
+}
 
 // HALO = 1: the split-buffer form. Arrays are subdomains with stored ghost layers on the axes
 // of g.hmask (Group), and the launch covers the box of tiles g.tlo + [0, g.tcnt) of each group;
 // the arithmetic per cell is the same as for the whole grid.
 template <int DIM, int EQ, int RECON, int FLUX, int BX, int BY, int BZ, int NT, int HOLD,
           int HALO = 0>
-__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(stage_min_waves<EQ, FLUX, HOLD>(), 8)))
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(stage_min_waves<DIM, EQ, RECON, FLUX, HOLD>(), 8)))
 stage_kernel(const StageArgs args)
 {
     using T = StageTile<DIM, EQ, RECON, BX, BY, BZ, NT>;
