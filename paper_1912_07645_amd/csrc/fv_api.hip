@@ -942,6 +942,8 @@ extern "C" fv_status fv_tune(fv_solver* s, double* state, int64_t batch, int32_t
     const int nv = fv_num_variants(s);
     if (reps < 1) reps = 3;
     HIP_TRY(hipSetDevice(s->device));
+    fv_status st = stream_enter(s);   // the copies below read what the caller's stream writes
+    if (st) return st;
     const size_t state_bytes = sizeof(double) * (size_t)batch * s->nf * s->cells;
     double* scratch = nullptr;
     HIP_TRY(hipMalloc((void**)&scratch, align256(state_bytes) + sizeof(double) * batch));
@@ -959,7 +961,7 @@ extern "C" fv_status fv_tune(fv_solver* s, double* state, int64_t batch, int32_t
         return e;
     };
     const int v0 = s->variant;
-    fv_status st = fv_set_variant(s, 0);
+    st = fv_set_variant(s, 0);
     // Steps per timed run: about 8 ms of work (between 4 and 32), the same for every variant.
     // Then about 50 ms of untimed steps, so that the clocks have left their idle state before
     // the first variant is timed (timed cold, the first variant would lose).
