@@ -31,6 +31,9 @@ struct GraphCache {
     std::vector<char> key;
 };
 
+// Statuses that fit the solver's pinned buffer (larger batches are read through the heap).
+constexpr int64_t kPinnedErr = 1024;
+
 struct fv_solver {
     fv_grid grid;
     fv_equation eq;
@@ -53,7 +56,7 @@ struct fv_solver {
     void* ws = nullptr;
     size_t ws_bytes = 0;
     bool ws_owned = true;
-    int32_t* host_count = nullptr;  // pinned
+    int32_t* host_count = nullptr;  // pinned: counts, then kPinnedErr statuses
     GraphCache graph;
     // kernel timing (fv_profile_enable)
     bool profile = false;
