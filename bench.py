@@ -136,17 +136,19 @@ def initial_state(w):
 
 
 # The sources that define the stage kernel of each benchmarked workload: the headers every
-# stage kernel compiles from, plus the instantiation unit that builds the workload's kernel. A
+# stage kernel compiles from, plus the instantiation units that build the workload's kernels. A
 # change to any of them invalidates that workload's committed traffic counters.
-STAGE_KERNEL_COMMON = ("fv_common.h", "fv_physics.h", "fv_registry.h", "fv_stage.h", "fv_stage_z.h")
-STAGE_KERNEL_UNIT = {"kh2d": "inst_euler2d_hot.hip", "kh3d": "inst_euler3d_hot.hip",
-                     "kh2d_roe": "inst_more2d.hip", "swe2d": "inst_swe.hip",
-                     "kh2d_godunov": "inst_godunov.hip", "kh2d_ec4": "inst_ec.hip",
-                     "mhd2d": "inst_mhd.hip"}
+STAGE_KERNEL_COMMON = ("fv_common.h", "fv_physics.h", "fv_fast.h", "fv_registry.h", "fv_stage.h",
+                       "fv_stage_y.h", "fv_stage_z.h")
+STAGE_KERNEL_UNIT = {"kh2d": ("inst_euler2d_hot.hip", "inst_rows2d.hip"),
+                     "kh3d": ("inst_euler3d_hot.hip", "inst_planes3d.hip"),
+                     "kh2d_roe": ("inst_more2d.hip",), "swe2d": ("inst_swe.hip",),
+                     "kh2d_godunov": ("inst_godunov.hip",), "kh2d_ec4": ("inst_ec.hip",),
+                     "mhd2d": ("inst_mhd.hip",)}
 
 
 def stage_kernel_sources(workload: str):
-    return STAGE_KERNEL_COMMON + (STAGE_KERNEL_UNIT[workload],)
+    return STAGE_KERNEL_COMMON + STAGE_KERNEL_UNIT[workload]
 
 
 def kernel_sources_hash(workload: str) -> str:
@@ -154,7 +156,7 @@ def kernel_sources_hash(workload: str) -> str:
 
 
 # The statistics pass: the sources of its kernels and the summary holding its counters.
-STATS_KERNEL_SOURCES = ("fv_common.h", "fv_stats.h", "fv_stats.hip")
+STATS_KERNEL_SOURCES = ("fv_common.h", "fv_stage.h", "fv_stage_y.h", "fv_stats.h", "fv_stats.hip")
 STATS_SUMMARY = "stats_mc_256x1024.md"
 
 
@@ -379,10 +381,9 @@ def run_adjoint(a, w):
     return out
 
 
-# LDS roof of the shell structure functions: every (cell, offset) term reads one double from
-# LDS (plus 3 FP64 operations, whose issue ceiling, 13.1e12 terms/s, lies above): 256 CUs x
-# 128 B per clock x 2.4 GHz / 8 B.
-SHELL_TERMS_PEAK = 256 * 128 * 2.4e9 / 8
+# FP64 issue roof of the shell structure functions: of the (cell, offset) terms, half are formed
+# (a pair serves both its ends), a subtraction and a fused multiply-add each.
+SHELL_TERMS_PEAK = FP64_LANE_OPS_PEAK
 
 
 def functionals(s, U, cells, B):
@@ -412,7 +413,7 @@ def functionals(s, U, cells, B):
     terms = N * B * s.num_quantities * sum(8 * h for h in range(1, H + 1))   # 2D cube shells
     out["shell_cube_h8_ms"] = ms
     out["shell_terms_per_s"] = terms / (ms * 1e-3)
-    out["shell_lds_roof_frac"] = terms / (ms * 1e-3) / SHELL_TERMS_PEAK
+    out["shell_fp64_roof_frac"] = terms / (ms * 1e-3) / SHELL_TERMS_PEAK
     return out
 
 
