@@ -237,7 +237,8 @@ extern "C" fv_status fv_adjoint_forward(fv_adjoint* a, const double* state0, dou
         SpeedArgs sp{};
         sp.ngroups = 1;
         sp.g[0] = stage_group(a, state0, state0, nullptr);
-        sp.nblocks = ((s->cells + s->kern->cells_per_block - 1) / s->kern->cells_per_block) * a->batch;
+        sp.cells_per_block = speed_block_cells(s->cells * a->batch, s->kern->cells_per_block);
+        sp.nblocks = ((s->cells + sp.cells_per_block - 1) / sp.cells_per_block) * a->batch;
         s->kern->speed(sp, st);
     }
     // rolling buffers: seg[0] holds the current state, seg[1..] the stage states

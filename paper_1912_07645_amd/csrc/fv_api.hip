@@ -480,12 +480,15 @@ static StepPlan make_plan(std::vector<GroupRun>& runs)
     for (size_t i = 0; i < runs.size(); ++i) p.ctrl.g[i] = make_ctrl(runs[i]);
     p.ctrl.n_running = (int32_t*)(runs[0].ws + runs[0].L.count);
     p.speed.ngroups = (int32_t)runs.size();
-    int64_t blocks = 0;
+    int64_t blocks = 0, cells = 0;
+    for (const GroupRun& r : runs) cells += r.s->cells * r.batch;
+    const int32_t per_block = speed_block_cells(cells, p.kern->cells_per_block);
+    p.speed.cells_per_block = per_block;
     for (size_t i = 0; i < runs.size(); ++i) {
         Group g = make_group(runs[i], 0, p.kern);
         g.src = runs[i].state;
         g.block0 = blocks;
-        const int64_t per = (runs[i].s->cells + p.kern->cells_per_block - 1) / p.kern->cells_per_block;
+        const int64_t per = (runs[i].s->cells + per_block - 1) / per_block;
         blocks += per * runs[i].batch;
         p.speed.g[i] = g;
     }

@@ -558,7 +558,8 @@ extern "C" fv_status fv_decomp_advance(fv_decomp* d, double* t, double t_end, do
             Group g = decomp_group(d, i, d->U[i], d->U[i], nullptr, zero, d->tiles);
             g.block0 = blocks;
             const int64_t owned = (int64_t)g.n[0] * g.n[1] * g.n[2];
-            blocks += (owned + d->hk->cells_per_block - 1) / d->hk->cells_per_block * g.batch;
+            if (i == 0) sp.cells_per_block = speed_block_cells(owned * P * g.batch, d->hk->cells_per_block);
+            blocks += (owned + sp.cells_per_block - 1) / sp.cells_per_block * g.batch;
             sp.g[sp.ngroups++] = g;
         }
         sp.nblocks = blocks;

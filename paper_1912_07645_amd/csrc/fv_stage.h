@@ -618,7 +618,7 @@ template <int DIM, int EQ, int HALO = 0>
 void launch_speed(const SpeedArgs& a, hipStream_t s)
 {
     hipLaunchKernelGGL((speed_kernel<DIM, EQ, HALO>), dim3((unsigned)a.nblocks), dim3(kThreads), 0,
-                       s, a, kSpeedCellsPerBlock);
+                       s, a, a.cells_per_block);
 }
 
 // Default LDS plan: split faces in 2D, fluxes held in registers otherwise.
