@@ -183,6 +183,7 @@ stage_kernel_y(const StageArgs args)
     double m = 0.0;
     bool bad = false;
 
+    wave_fence();   // the ends of every row are in LDS
 #pragma unroll 1
     for (int32_t k = y0; k < y1; ++k) {
         // 1. the row into LDS, its ends by the first lanes; request the cell G rows up
