@@ -32,6 +32,7 @@ namespace fvk {
 constexpr int kFnThreads = 256;
 constexpr int kShellMaxH = 64;
 constexpr int kShellTile2 = 64;    // side of the register-tiled 2D shell kernel's tile
+constexpr int kShellBlocks2 = 16;  // blocks of 16 x 16 cells in it
 constexpr int kShellMaxH2 = 16;    // and its largest radius (61 KB of LDS; beyond, one cell per thread)
 
 // kind: 0 the field itself; 1 Euler (momenta over rho); 2 shallow water (momenta over h);
@@ -129,7 +130,7 @@ __device__ __forceinline__ double shell_add(double acc, double d)
 // so of every such pair one offset is taken (the first nonzero of oz, oy, ox positive), and the
 // sum over the shell is twice that over its half: half the terms.
 
-// One cell per thread (1D, 3D, and 2D radii beyond the register-tiled kernel below).
+// One cell per thread (1D, 3D, and 2D where the kernels below do not apply).
 template <int DIM, int P>
 __global__ void __launch_bounds__(kFnThreads) shell_kernel(const ShellArgs a)
 {
@@ -196,6 +197,45 @@ __global__ void __launch_bounds__(kFnThreads) shell_kernel(const ShellArgs a)
         for (int w = 1; w < kFnThreads / 64; ++w) s = s + wsum[w * H + h];
         a.partial[(sq * H + h) * a.ntiles + tile] = s;
     }
+}
+
+// The offsets of half a 2D shell in the order that both 2D kernels below take them for a cell:
+// row(oy, lo, hi) takes (lo, oy) .. (hi, oy), column(ox, hi) takes (ox, 1) .. (ox, hi).
+template <bool BALL, class Row, class Column>
+__device__ __forceinline__ void shell2d_half(int h, const Row& row, const Column& column)
+{
+    if constexpr (BALL) {
+        // (h - 1)^2 < ox^2 + oy^2 <= h^2: of row oy the columns lo..hi and -hi..-lo
+        int hi = h, lo = h;
+#pragma unroll 1
+        for (int oy = 0; oy <= h; ++oy) {
+            while (hi * hi > h * h - oy * oy) --hi;
+            const int inner = (h - 1) * (h - 1) - oy * oy;
+            if (inner < 0) {
+                row(oy, -hi, hi);
+            } else {
+                while (lo > 1 && (lo - 1) * (lo - 1) > inner) --lo;
+                if (lo <= hi) {
+                    row(oy, lo, hi);
+                    if (oy > 0) row(oy, -hi, -lo);
+                }
+            }
+        }
+    } else {
+        row(h, -h, h);
+        column(h, h - 1);
+        column(-h, h - 1);
+        row(0, h, h);
+    }
+}
+
+// The sum over a 64 x 64 tile, in the order that both 2D kernels take: 4 x 4 cells pairwise, by
+// columns, then rows; four such squares along x pairwise, then four along y (a block of 16 x 16);
+// four blocks along x pairwise; the four rows of blocks in order. Cells and blocks outside the
+// grid add +0 to sums of terms >= +0. The tiles are added in order by the second pass.
+__device__ __forceinline__ double pairwise4(double a, double b, double c, double d)
+{
+    return (a + b) + (c + d);
 }
 
 // 2D, radii up to HM: 64 x 64 cells to a workgroup, 4 x 4 to a thread. What bounded one cell per
@@ -354,36 +394,18 @@ shell2d_kernel(const ShellArgs a)
         for (int r = 0; r < 4; ++r)
 #pragma unroll
             for (int j = 0; j < 4; ++j) acc[r][j] = 0.0;
-        if constexpr (BALL) {
-            // (h - 1)^2 < ox^2 + oy^2 <= h^2: of row oy the columns lo..hi and -hi..-lo
-            int hi = h, lo = h;
-#pragma unroll 1
-            for (int oy = 0; oy <= h; ++oy) {
-                while (hi * hi > h * h - oy * oy) --hi;
-                const int inner = (h - 1) * (h - 1) - oy * oy;
-                if (inner < 0) {
-                    along_row(oy, -hi, hi);
-                } else {
-                    while (lo > 1 && (lo - 1) * (lo - 1) > inner) --lo;
-                    if (lo <= hi) {
-                        along_row(oy, lo, hi);
-                        if (oy > 0) along_row(oy, -hi, -lo);
-                    }
-                }
-            }
-        } else {
-            along_row(h, -h, h);
-            along_column(h, h - 1);
-            along_column(-h, h - 1);
-            along_row(0, h, h);
+        shell2d_half<BALL>(h, along_row, along_column);
+        double row[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[r][j] = (in_x[j] && in_y[r]) ? acc[r][j] : 0.0;
+            row[r] = pairwise4(acc[r][0], acc[r][1], acc[r][2], acc[r][3]);
         }
-        double sum = 0.0;
+        double sum = pairwise4(row[0], row[1], row[2], row[3]);
+        constexpr int order[6] = {1, 2, 16, 32, 4, 8};   // 4 threads along x, 4 along y, 4 blocks
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) sum = sum + ((in_x[j] && in_y[r]) ? acc[r][j] : 0.0);
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) sum = sum + __shfl_xor(sum, off, 64);
+        for (int i = 0; i < 6; ++i) sum = sum + __shfl_xor(sum, order[i], 64);
         if (lane == 0) wsum[wave * H + (h - 1)] = sum;
     }
     __syncthreads();
@@ -394,10 +416,73 @@ shell2d_kernel(const ShellArgs a)
     }
 }
 
+// The same for too few tiles to keep the chip busy, bit for bit: one cell per thread, one of a
+// tile's sixteen 16 x 16 blocks to a workgroup (ntiles counts blocks); a call of a few tiles is
+// bound by the longest workgroup, and this one's is a sixteenth (figures at the choice, in
+// fv_structure_shell). Lane bits 0 and 1 are the
+// column and 2 and 3 the row in a square of 4 x 4 cells, bits 4 and 5 the square along x, the
+// wavefront is the square along y.
+template <int P, bool BALL>
+__global__ void __launch_bounds__(kFnThreads) shell2d_cell_kernel(const ShellArgs a)
+{
+    constexpr int T = 16;
+    extern __shared__ double lds[];
+    const int H = a.H, PX = T + 2 * H, rows = T + H;
+    double* wsum = lds + rows * PX;         // [waves][H]
+
+    const int64_t blk = blockIdx.x;
+    const int32_t block = (int32_t)(blk % a.ntiles), tile = block / kShellBlocks2;
+    const int64_t sq = blk / a.ntiles;      // sample * nq + quantity
+    const int qi = (int)(sq % a.nq);
+    const double* U = a.state + (sq / a.nq) * a.nf * a.cells;
+    const int32_t x0 = (tile % a.tiles[0]) * kShellTile2 + (block & 3) * T;
+    const int32_t y0 = (tile / a.tiles[0]) * kShellTile2 + ((block >> 2) & 3) * T;
+    double* out = a.partial + sq * H * a.ntiles + block;   // one per radius, ntiles apart
+    if (x0 >= a.n[0] || y0 >= a.n[1]) {   // uniform
+        for (int h = threadIdx.x; h < H; h += kFnThreads) out[(int64_t)h * a.ntiles] = 0.0;
+        return;
+    }
+
+    for (int e = threadIdx.x; e < rows * PX; e += kFnThreads) {
+        const int px = e % PX, py = e / PX;
+        const int32_t gx = wrap_index(x0 + px - H, a.n[0], BC_PERIODIC);
+        const int32_t gy = wrap_index(y0 + py, a.n[1], BC_PERIODIC);
+        lds[e] = quantity_at(U, a.cells, a.nf, a.kind, (int64_t)gy * a.n[0] + gx, qi);
+    }
+    __syncthreads();
+
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int cx = 4 * (lane >> 4) + (lane & 3), cy = 4 * wave + ((lane >> 2) & 3);
+    const bool inside = x0 + cx < a.n[0] && y0 + cy < a.n[1];
+    const double* own = lds + cy * PX + (cx + H);
+    const double q0 = own[0];
+#pragma unroll 1
+    for (int h = 1; h <= H; ++h) {
+        double acc = 0.0;
+        shell2d_half<BALL>(
+            h,
+            [&](int oy, int lo, int hi) {
+                const double* p = own + oy * PX;
+                for (int ox = lo; ox <= hi; ++ox) acc = shell_add<P>(acc, p[ox] - q0);
+            },
+            [&](int ox, int hi) {
+                const double* p = own + ox;
+                for (int oy = 1; oy <= hi; ++oy) acc = shell_add<P>(acc, p[oy * PX] - q0);
+            });
+        double sum = inside ? acc : 0.0;
+#pragma unroll
+        for (int off = 1; off <= 32; off *= 2) sum = sum + __shfl_xor(sum, off, 64);
+        if (lane == 0) wsum[wave * H + (h - 1)] = sum;
+    }
+    __syncthreads();
+    for (int h = threadIdx.x; h < H; h += kFnThreads)
+        out[(int64_t)h * a.ntiles] = pairwise4(wsum[h], wsum[H + h], wsum[2 * H + h], wsum[3 * H + h]);
+}
+
 struct ShellFinishArgs {
     const double* partial;   // [rows][ntiles], row = (sample * nq + q) * H + h - 1
     int64_t rows;
-    int32_t ntiles, H;
+    int32_t ntiles, H, blocks; // blocks: partials are the 16 blocks of every tile
     double cells;
     double shell[kShellMaxH];  // |A_h| / 2
     double* out;             // [rows]
@@ -408,8 +493,17 @@ __global__ void __launch_bounds__(kFnThreads) shell_finish_kernel(const ShellFin
     const int64_t r = (int64_t)blockIdx.x * kFnThreads + threadIdx.x;
     if (r >= a.rows) return;
     const double* p = a.partial + r * a.ntiles;
-    double s = p[0];
-    for (int t = 1; t < a.ntiles; ++t) s = s + p[t];
+    double s = 0.0;   // sums of terms >= +0
+    if (a.blocks) {
+        for (int t = 0; t < a.ntiles; t += kShellBlocks2) {
+            double tile = 0.0;
+            for (int k = t; k < t + kShellBlocks2; k += 4)
+                tile = tile + pairwise4(p[k], p[k + 1], p[k + 2], p[k + 3]);
+            s = s + tile;
+        }
+    } else {
+        for (int t = 0; t < a.ntiles; ++t) s = s + p[t];
+    }
     a.out[r] = s / (a.cells * a.shell[r % a.H]);
 }
 
@@ -417,6 +511,16 @@ template <int DIM, int P>
 static void launch_shell(const ShellArgs& a, int64_t blocks, size_t lds, hipStream_t s)
 {
     hipLaunchKernelGGL((shell_kernel<DIM, P>), dim3((unsigned)blocks), dim3(kFnThreads), lds, s, a);
+}
+
+static void launch_shell2d_cells(const ShellArgs& a, int order, int64_t blocks, hipStream_t s)
+{
+    const size_t lds = sizeof(double) * (size_t)((16 + a.H) * (16 + 2 * a.H) + (kFnThreads / 64) * a.H);
+    const dim3 grid((unsigned)blocks), block(kFnThreads);
+    if (order == 1 && a.ball) hipLaunchKernelGGL((shell2d_cell_kernel<1, true>), grid, block, lds, s, a);
+    else if (order == 1) hipLaunchKernelGGL((shell2d_cell_kernel<1, false>), grid, block, lds, s, a);
+    else if (a.ball) hipLaunchKernelGGL((shell2d_cell_kernel<2, true>), grid, block, lds, s, a);
+    else hipLaunchKernelGGL((shell2d_cell_kernel<2, false>), grid, block, lds, s, a);
 }
 
 template <int HM>
@@ -535,24 +639,29 @@ extern "C" fv_status fv_structure_shell(const fv_solver* s, const double* state,
     const int64_t P[3] = {T[0] + 2 * max_h, dim >= 2 ? T[1] + 2 * max_h : 1, dim >= 3 ? T[2] + 2 * max_h : 1};
     const size_t lds = sizeof(double) * (size_t)(P[0] * P[1] * P[2] + (kFnThreads / 64) * max_h);
     if (lds > 65536) return fail(FV_ENOTSUP, "max_h too large for this dimension (tile and halo exceed 64 KB of LDS)");
-    // The register-tiled kernel, where its tiles are at least a quarter full and are enough to keep
-    // the chip busy. us, one cell per thread -> 4 x 4 (4 quantities, radius 8): 64 samples of 256^2
-    // (4096 workgroups) 1096 -> 348, 64 of 40^2 (256, 39% full) 74 -> 56; 64 of 20^2 (256, 10%
-    // full) 53 -> 67, one of 64^2 (4) 45 -> 65. The one-cell kernel takes
-    // five times as long for ball shells (256^2: 4993 -> 395).
+    // 2D, radii up to kShellMaxH2, tiles of 64 x 64 at least a quarter full: 4 x 4 cells per thread
+    // where that makes enough workgroups to keep the chip busy, else one cell per thread with the
+    // same sums, so results do not depend on the batch. us, one cell per thread -> 4 x 4 (4
+    // quantities, radius 8, cube / ball shells): one sample of 64^2 (4 workgroups of tiles) 69 -> 88
+    // / 69 -> 101, 256^2 (64) 70 -> 78 / 76 -> 90, 7 of 128^2 (112) 80 -> 79 / 91 -> 91, two of
+    // 256^2 (128) 86 -> 78 / 92 -> 86, 64 of 40^2 (256, 39% full) 109 -> 78 / 117 -> 91, 64 of
+    // 256^2 (4096) 998 -> 328 / 1112 -> 364; radius 16, two of 128^2 (32) 80 -> 130 / 107 -> 182.
+    // Below a quarter, 64 of 20^2 (256, 10% full) took 53 us in tiles of 16 x 16 and 67 in tiles of
+    // 64 x 64 (cube).
     const int64_t tiles64 = ((s->grid.n[0] + kShellTile2 - 1) / kShellTile2) * ((s->grid.n[1] + kShellTile2 - 1) / kShellTile2);
-    const bool wide = dim == 2 && max_h <= kShellMaxH2 &&
-                      4 * s->cells >= tiles64 * kShellTile2 * kShellTile2 &&
-                      batch * num_quantities(s) * tiles64 >= (ball ? 32 : 128);
+    const bool tiled = dim == 2 && max_h <= kShellMaxH2 &&
+                       4 * s->cells >= tiles64 * kShellTile2 * kShellTile2;
+    const bool wide = tiled && batch * num_quantities(s) * tiles64 >= 128;
     ShellArgs a{};
     a.cells = s->cells;
     a.ntiles = 1;
     for (int k = 0; k < 3; ++k) {
-        const int tk = (wide && k < 2) ? kShellTile2 : T[k];
+        const int tk = (tiled && k < 2) ? kShellTile2 : T[k];
         a.n[k] = (int32_t)s->grid.n[k];
         a.tiles[k] = (int32_t)((s->grid.n[k] + tk - 1) / tk);
         a.ntiles *= a.tiles[k];
     }
+    if (tiled && !wide) a.ntiles *= kShellBlocks2;
     a.nf = s->nf;
     a.kind = quantity_kind(s);
     a.nq = num_quantities(s);
@@ -561,6 +670,7 @@ extern "C" fv_status fv_structure_shell(const fv_solver* s, const double* state,
     ShellFinishArgs f{};
     f.ntiles = a.ntiles;
     f.H = max_h;
+    f.blocks = tiled && !wide;
     f.cells = (double)s->cells;
     for (int h = 1; h <= max_h; ++h) f.shell[h - 1] = 0.5 * (double)shell_size(dim, h, ball);
     // samples per pass: partial sums of at most 2^22 doubles (32 MiB)
@@ -581,6 +691,8 @@ extern "C" fv_status fv_structure_shell(const fv_solver* s, const double* state,
         if (wide) {
             if (max_h <= 8) launch_shell2d<8>(a, order, blocks, sm->stream);
             else launch_shell2d<kShellMaxH2>(a, order, blocks, sm->stream);
+        } else if (tiled) {
+            launch_shell2d_cells(a, order, blocks, sm->stream);
         } else switch (dim * 10 + order) {
             case 11: launch_shell<1, 1>(a, blocks, lds, sm->stream); break;
             case 12: launch_shell<1, 2>(a, blocks, lds, sm->stream); break;
