@@ -212,11 +212,14 @@ fv_status fv_evolve_multi(int32_t n_groups, fv_solver* const* solvers, double* c
  * one (64 columns by 8 or 16 rows, 16 x 15 columns by 16 planes; listed like the others).
  * fv_num_variants returns their number (-1 on NULL); fv_set_variant selects one (FV_EINVAL
  * if out of range); fv_get_tile reports the selected tile shape in cells and its variant
- * index (any output may be NULL). */
+ * index (any output may be NULL); fv_last_variant returns the variant that the solver's last
+ * stepping call ran (fv_evolve_multi: the one it began with), -1 before the first and on
+ * NULL. */
 int32_t fv_num_variants(const fv_solver* solver);
 fv_status fv_set_variant(fv_solver* solver, int32_t variant);
 fv_status fv_get_tile(const fv_solver* solver, int32_t* bx, int32_t* by, int32_t* bz,
                       int32_t* variant);
+int32_t fv_last_variant(const fv_solver* solver);
 
 /* Autotuner: after about 50 ms of untimed warm-up steps, time runs of 4 to 32 whole steps
  * (about 8 ms each) of every variant on a copy of `state` (device, [batch][fields][cells],

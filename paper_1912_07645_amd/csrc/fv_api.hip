@@ -436,6 +436,14 @@ static bool march_pays(const std::vector<GroupRun>& runs)
     return tiles >= (k->march == kMarchRows ? 3 * 4096 : 640);
 }
 
+// Index of a kernel among the variants of the solver's scheme.
+static int32_t variant_of(const fv_solver* s, const StageKernel* kern)
+{
+    int32_t v = 0;
+    while (find_stage_kernel(s->grid.dim, s->eq.kind, s->recon, s->flux, v) != kern) ++v;
+    return v;
+}
+
 static StepPlan make_plan(std::vector<GroupRun>& runs)
 {
     StepPlan p;
@@ -558,6 +566,7 @@ static fv_status run_steps(fv_solver* s0, std::vector<GroupRun> runs, const Ctrl
     hipStream_t st = s0->stream;
     const int64_t max_steps = cp.max_steps;
     StepPlan p = make_plan(runs);
+    for (GroupRun& r : runs) r.s->ran = variant_of(s0, p.kern);
     apply_params(p, cp);
     int32_t* counts_dev = p.ctrl.n_running;
     launch_ctrl_reset(p.ctrl, st);
@@ -721,6 +730,7 @@ static fv_status evolve_common(fv_solver* s, double* state, int64_t batch, doubl
         if (st) return st;
         st = stream_enter(s);
         if (st) return st;
+        s->ran = s->variant;
         char* sc = (char*)s->scratch;
         SmallArgs a{};
         a.state = state;
@@ -961,6 +971,8 @@ extern "C" fv_status fv_get_tile(const fv_solver* s, int32_t* bx, int32_t* by, i
     if (variant) *variant = s->variant;
     return FV_OK;
 }
+
+extern "C" int32_t fv_last_variant(const fv_solver* s) { return s ? s->ran : -1; }
 
 // Time runs of whole steps (all Runge--Kutta stages) of every tile variant on `state` for
 // `batch` samples and keep the variant with the fastest median run. The state is not

@@ -63,6 +63,7 @@ def _load():
         "fv_num_variants": (i32, [vp]),
         "fv_set_variant": (i32, [vp, i32]),
         "fv_get_tile": (i32, [vp, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32), C.POINTER(i32)]),
+        "fv_last_variant": (i32, [vp]),
         "fv_tune": (i32, [vp, vp, i64, i32, C.POINTER(i32)]),
         "fv_stats_create": (i32, [vp, i32, C.POINTER(vp)]),
         "fv_stats_accumulate": (i32, [vp, vp, i64]),
@@ -246,6 +247,10 @@ def fv_get_tile(solver):
     bx, by, bz, v = C.c_int32(), C.c_int32(), C.c_int32(), C.c_int32()
     check(lib.fv_get_tile(solver, C.byref(bx), C.byref(by), C.byref(bz), C.byref(v)), "fv_get_tile")
     return (bx.value, by.value, bz.value), v.value
+
+
+def fv_last_variant(solver) -> int:
+    return lib.fv_last_variant(solver)
 
 
 def fv_tune(solver, state, batch, reps=3) -> int:

@@ -138,6 +138,11 @@ class Solver:
     def tile(self):
         return fv.fv_get_tile(self.handle)
 
+    def last_variant(self) -> int:
+        """Variant that the last stepping call ran (-1 before the first): the selected one, or
+        the marching one where the library chose it by size."""
+        return fv.fv_last_variant(self.handle)
+
     def tune(self, U, reps=3) -> int:
         B = self._check_state(U)
         self._prepare(B)
