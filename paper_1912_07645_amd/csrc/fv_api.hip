@@ -1004,6 +1004,8 @@ extern "C" fv_status fv_tune(fv_solver* s, double* state, int64_t batch, int32_t
         return e;
     };
     const int v0 = s->variant;
+    const bool set0 = s->variant_set;
+    const StageKernel* kern0 = s->kern;
     st = fv_set_variant(s, 0);
     // Steps per timed run: about 8 ms of work (between 4 and 32), the same for every variant.
     // Then about 50 ms of untimed steps, so that the clocks have left their idle state before
@@ -1037,8 +1039,11 @@ extern "C" fv_status fv_tune(fv_solver* s, double* state, int64_t batch, int32_t
     }
     hipFree(scratch);
     if (st) {
+        const std::string msg = g_last_error;
         fv_set_variant(s, v0);
-        return st;
+        s->variant_set = set0;
+        s->kern = kern0;
+        return fail(st, msg);
     }
     st = fv_set_variant(s, best_v);
     if (chosen) *chosen = best_v;
