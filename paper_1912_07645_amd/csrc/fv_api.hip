@@ -406,7 +406,7 @@ struct StepPlan {
     const StageKernel* kern = nullptr;
 };
 
-// Whether a solver left to its default runs the marching kernel of its scheme: on enough tiles
+// Whether solvers left to their default run the marching kernel of their scheme: on enough tiles
 // to fill the chip, whose columns are at least four fifths full on every grid. us per step,
 // tile -> march.
 // By rows (2D, a wavefront to a tile; three rounds of the 4096 that fit): WENO3 + HLLC, 256^2 x
@@ -421,9 +421,10 @@ static bool march_pays(const std::vector<GroupRun>& runs)
 {
     const fv_solver* s0 = runs[0].s;
     const StageKernel* k = s0->march;
-    if (!k || s0->variant_set) return false;
+    if (!k) return false;
     int64_t tiles = 0;
     for (const GroupRun& r : runs) {
+        if (r.s->variant_set) return false;
         const int64_t* n = r.s->grid.n;
         int64_t t[3];
         const int32_t b[3] = {k->bx, k->by, k->bz};
