@@ -243,7 +243,7 @@ extern "C" fv_status fv_create(const fv_grid* grid, const fv_equation* eq, int32
     hipError_t e = hipGetDevice(&s->device);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&s->stream, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&s->ev, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipHostMalloc((void**)&s->host_count, sizeof(int32_t) * (1 + kMaxGroups + kPinnedErr), hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc((void**)&s->host_count, sizeof(int32_t) * (2 + kMaxGroups + kPinnedErr), hipHostMallocDefault);
     if (e != hipSuccess) {
         fv_destroy(s);
         return fail(FV_EDEVICE, std::string("fv_create: ") + hipGetErrorString(e));
@@ -556,10 +556,13 @@ static void apply_params(StepPlan& p, const CtrlParams& c)
 // again, so finished coarse levels stop costing launch slots.
 //
 // A synchronisation leaves the device idle for about 20 us, as long as a step of a small grid, so
-// a single run of at most one chunk starts without waiting for its first count (if nothing runs,
-// its launches find no active sample), and with `unread` the last count of a run limited by
-// max_steps is only queued to be copied: the caller, which synchronises to read the statuses,
-// checks it then (97 x 61, 10 steps: 278 -> 245 us).
+// a single run of at most one chunk enqueues its first step behind the first decision, which also
+// stores its count in host memory, and reads that count while the device works; if nothing runs the
+// call ends there. With `unread` the last count of a run limited by max_steps is only queued to be
+// copied: the caller, which synchronises to read the statuses, checks it then. us per call: 97 x 61,
+// 10 steps, 278 with both waits, 243 now (254 with no step enqueued ahead, 248 with two, 244 with
+// an event in the place of the stored count, 239 with no look at the count at all); 1024^2, nothing
+// to do, limit of 16 steps, 95 with both waits, 100 now (291 with no look at the count).
 static fv_status run_steps(fv_solver* s0, std::vector<GroupRun> runs, const CtrlParams& cp,
                            const std::vector<char>& key0, bool eager_only = false,
                            bool* unread = nullptr)
@@ -572,10 +575,18 @@ static fv_status run_steps(fv_solver* s0, std::vector<GroupRun> runs, const Ctrl
     int32_t* counts_dev = p.ctrl.n_running;
     launch_ctrl_reset(p.ctrl, st);
     p.kern->speed(p.speed, st);
-    launch_ctrl_begin(p.ctrl, st);
-    HIP_TRY(hipGetLastError());
-    const int64_t chunk = chunk_steps(max_steps);
+    int64_t chunk = chunk_steps(max_steps);
     const bool profile = s0->profile && !eager_only;
+    const bool single = runs.size() == 1 && !profile;
+    const bool brief = single && max_steps >= 1 && max_steps <= chunk;
+    CtrlArgs first = p.ctrl;
+    volatile int32_t* now = s0->host_count + 1 + kMaxGroups + kPinnedErr;
+    if (brief) {
+        *now = -1;
+        first.host_running = (int32_t*)now;
+    }
+    launch_ctrl_begin(first, st);
+    HIP_TRY(hipGetLastError());
     const bool use_graph = graphs_enabled() && !profile && !eager_only;
     const size_t nst = p.stages.size();
     if (profile) {
@@ -593,14 +604,24 @@ static fv_status run_steps(fv_solver* s0, std::vector<GroupRun> runs, const Ctrl
         if (wait) HIP_TRY(hipStreamSynchronize(st));
         return FV_OK;
     };
-    const bool single = runs.size() == 1 && !profile;
     fv_status e = FV_OK;
-    if (!single || max_steps < 1 || max_steps > chunk) {
+    int64_t done = 0;
+    if (brief) {
+        enqueue_step(p, st);
+        HIP_TRY(hipGetLastError());
+        for (int64_t i = 1; *now < 0; ++i) {
+            if (i % 1024 != 0 || hipStreamQuery(st) == hipErrorNotReady) continue;
+            HIP_TRY(hipStreamSynchronize(st));   // all done, or a launch failed
+            if (*now < 0) return fail(FV_EDEVICE, "the first step decision left no count");
+        }
+        if (*now == 0) return FV_OK;
+        done = 1;
+        chunk = std::max<int64_t>(1, max_steps - 1);   // the graph's steps
+    } else {
         e = read_counts(true);
         if (e) return e;
         if (s0->host_count[0] == 0) return FV_OK;
     }
-    int64_t done = 0;
     while (done < max_steps) {
         // drop groups that have finished (multi-group runs only)
         if (runs.size() > 1) {
@@ -641,13 +662,9 @@ static fv_status run_steps(fv_solver* s0, std::vector<GroupRun> runs, const Ctrl
             HIP_TRY(hipGetLastError());
         }
         done += n;
-        const bool defer = unread && single && done >= max_steps;
-        e = read_counts(!defer);
+        if (unread && single && done >= max_steps) break;
+        e = read_counts(true);
         if (e) return e;
-        if (defer) {
-            *unread = true;
-            return FV_OK;
-        }
         if (profile) {
             for (size_t i = 0; i < (size_t)n; ++i) {
                 float ms = 0.0f;
@@ -658,7 +675,11 @@ static fv_status run_steps(fv_solver* s0, std::vector<GroupRun> runs, const Ctrl
         }
         if (s0->host_count[0] == 0) return FV_OK;
     }
-    return fail(FV_EDEVICE, kNoEnd);
+    e = read_counts(!unread);
+    if (e) return e;
+    if (unread) *unread = true;
+    else if (s0->host_count[0] != 0) return fail(FV_EDEVICE, kNoEnd);
+    return FV_OK;
 }
 
 // queued: the statuses of at most kPinnedErr samples have been copied behind the counts already.

@@ -28,6 +28,7 @@ struct CtrlArgs {
     double cfl_bound;
     int64_t max_steps;
     int32_t* n_running;      // out: [0] samples taking the step just decided, [1 + g] per group
+    int32_t* host_running;   // host memory, or null: n_running[0] also there
 };
 
 struct CopyGroup {

@@ -102,6 +102,8 @@ __global__ void __launch_bounds__(1024) ctrl_begin_kernel(const CtrlArgs a)
             a.n_running[1 + gi] = count[gi];
         }
         a.n_running[0] = total;
+        if (a.host_running)
+            __hip_atomic_store(a.host_running, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 

@@ -57,7 +57,8 @@ struct fv_solver {
     void* ws = nullptr;
     size_t ws_bytes = 0;
     bool ws_owned = true;
-    int32_t* host_count = nullptr;  // pinned: counts, then kPinnedErr statuses
+    // pinned: counts, then kPinnedErr statuses, then the first count of a short run
+    int32_t* host_count = nullptr;
     GraphCache graph;
     // kernel timing (fv_profile_enable)
     bool profile = false;
