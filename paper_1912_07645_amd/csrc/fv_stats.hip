@@ -107,7 +107,6 @@ welford_kernel(const double* __restrict__ state, int64_t cells, int32_t batch, i
 //
 // Beyond 64 x 32 lags a pass is repeated with the rings delayed by h0 - 1 cells, which takes a
 // second stream of the line's values (DELAY).
-constexpr int kSfBatch = 4;    // march steps between requests
 constexpr int kSfChunk = 8;    // columns staged at a time (lines along x)
 constexpr int kSfPitch = kSfChunk + 1;
 constexpr int kSfAlone = 48;   // lags of a lane that has a segment to itself
@@ -162,13 +161,14 @@ struct SfArgs {
 };
 
 // A line along y or z: a stream of its values from some position on, four steps ahead.
+template <int B>
 struct SfColumn {
     const double* q;       // the field
     const double* rho;     // field 0
     int32_t stride, span;  // of a line, in cells (cells < 2^31)
     uint32_t at, end;      // the lane's next cell to request; the cell past its line
     bool div;
-    double v[kSfBatch], r[kSfBatch], cur[kSfBatch];
+    double v[B], r[B], cur[B];
 
     template <int G>
     __device__ __forceinline__ void load(double (&x)[G], double (&y)[G])
@@ -206,25 +206,26 @@ struct SfColumn {
 #pragma unroll
         for (int i = 0; i < G; ++i) out[i] = z[i];
     }
-    __device__ __forceinline__ void begin(double*) { fetch<kSfBatch>(cur, nullptr); }
-    __device__ __forceinline__ void request() { load<kSfBatch>(v, r); }
-    __device__ __forceinline__ void take(double (&out)[kSfBatch], double*)
+    __device__ __forceinline__ void begin(double*) { fetch<B>(cur, nullptr); }
+    __device__ __forceinline__ void request() { load<B>(v, r); }
+    __device__ __forceinline__ void take(double (&out)[B], double*)
     {
 #pragma unroll
-        for (int i = 0; i < kSfBatch; ++i) out[i] = cur[i];
+        for (int i = 0; i < B; ++i) out[i] = cur[i];
     }
-    __device__ __forceinline__ void commit(double*) { finish<kSfBatch>(cur, v, r); }
+    __device__ __forceinline__ void commit(double*) { finish<B>(cur, v, r); }
 };
 
 // The same for lines along x, through LDS (buf: two chunks of 64 segments x kSfPitch).
+template <int B>
 struct SfRow {
     const double* q;       // the field
     const double* rho;
     const int2* seg;       // per segment of the wavefront: first cell of its line, first column
     int32_t n, y;          // cells of a line; next chunk's distance from the segment's first, mod n
     bool div;
-    int32_t half, side;    // half of the chunk at hand; buffer it is in
-    double v[kSfBatch], r[kSfBatch];
+    int32_t half, side;    // B cells of the chunk at hand; buffer it is in
+    double v[B], r[B];
 
     static __device__ __forceinline__ int32_t slot(int k) { return k * 8 + ((threadIdx.x & 63) >> 3); }
 
@@ -293,17 +294,17 @@ struct SfRow {
         wave_fence();
         half = side = 0;
     }
-    __device__ __forceinline__ void request() { load<kSfBatch>(v, r, half * kSfBatch); }
-    __device__ __forceinline__ void take(double (&out)[kSfBatch], double* buf)
+    __device__ __forceinline__ void request() { load<B>(v, r, half * B); }
+    __device__ __forceinline__ void take(double (&out)[B], double* buf)
     {
-        const double* p = buf + (side * 64 + (threadIdx.x & 63)) * kSfPitch + half * kSfBatch;
+        const double* p = buf + (side * 64 + (threadIdx.x & 63)) * kSfPitch + half * B;
 #pragma unroll
-        for (int i = 0; i < kSfBatch; ++i) out[i] = p[i];
+        for (int i = 0; i < B; ++i) out[i] = p[i];
     }
     __device__ __forceinline__ void commit(double* buf)
     {
-        store<kSfBatch>(v, r, buf + (side ^ 1) * 64 * kSfPitch, half * kSfBatch);
-        half ^= 1;
+        store<B>(v, r, buf + (side ^ 1) * 64 * kSfPitch, half * B);
+        half = half + 1 < kSfChunk / B ? half + 1 : 0;
         if (half == 0) {
             side ^= 1;
             advance();
@@ -321,10 +322,10 @@ __device__ __forceinline__ void sf_fill(Line& line, double (&ring)[W], double* b
     if constexpr (W % 16 != 0) line.template fetch<8>(ring + W / 16 * 16, buf);
 }
 
-// Sums over the wavefront of W accumulators per lane, in a fixed order: a transposing butterfly
-// halves the lags that a lane holds at each step (the lane keeps the half that its bit selects and
-// adds the partner's copy of it); the remaining steps finish the sums. The sum of lag h0 + l ends
-// in the lanes l * 64 / W and following.
+// Sums over the wavefront of W accumulators per lane, in a fixed order (neighbouring lanes first): a
+// transposing butterfly halves the lags that a lane holds at each step (the lane keeps the half
+// that its bit selects and adds the partner's copy of it); the remaining steps finish the sums.
+// The sum of lag h0 + l ends in the lane whose low bits, reversed, are l.
 template <int H, int M, int W>
 __device__ __forceinline__ void sf_wave_sum(double (&v)[W])
 {
@@ -336,10 +337,10 @@ __device__ __forceinline__ void sf_wave_sum(double (&v)[W])
             const double give = up ? v[k] : v[H + k];
             v[k] = keep + __shfl_xor(give, M);
         }
-        sf_wave_sum<H / 2, M / 2>(v);
-    } else if constexpr (M >= 1) {
+        sf_wave_sum<H / 2, 2 * M>(v);
+    } else if constexpr (M <= 32) {
         v[0] = v[0] + __shfl_xor(v[0], M);
-        sf_wave_sum<0, M / 2>(v);
+        sf_wave_sum<0, 2 * M>(v);
     }
 }
 
@@ -354,7 +355,7 @@ __device__ __forceinline__ double sf_from_left(double x)
 
 // a: the stream from the segment's first cell; d (DELAY): the same, delayed. ring: the W cells
 // ahead of them; head: first lane of a segment; len: cells of the lane's segment, most: of any.
-template <int W, bool MULTI, bool DELAY, class Line>
+template <int W, int B, bool MULTI, bool DELAY, class Line>
 __device__ __forceinline__ void sf_march(Line& a, Line& d, double* abuf, double* dbuf, bool head,
                                          int32_t len, int32_t most, double (&ring)[W],
                                          double (&acc)[W])
@@ -364,15 +365,15 @@ __device__ __forceinline__ void sf_march(Line& a, Line& d, double* abuf, double*
 #pragma unroll 1
     for (int32_t y = 0; y < most; y += W) {
 #pragma unroll
-        for (int s0 = 0; s0 < W; s0 += kSfBatch) {
+        for (int s0 = 0; s0 < W; s0 += B) {
             if (y + s0 < most) {   // uniform
-                double v[kSfBatch], r[kSfBatch];
+                double v[B], r[B];
                 a.request();
                 if (DELAY) d.request();
                 a.take(v, abuf);
                 if (DELAY) d.take(r, dbuf);
 #pragma unroll
-                for (int i = 0; i < kSfBatch; ++i) {
+                for (int i = 0; i < B; ++i) {
                     const int s = s0 + i;
                     if (y + s < len) {
 #pragma unroll
@@ -404,9 +405,12 @@ __device__ __forceinline__ void sf_march(Line& a, Line& d, double* abuf, double*
     }
 }
 
-template <int W, bool MULTI, bool DELAY, bool ROWS>
+// B: march steps between requests. With 8 lags a step is short against a load: 8 at a time (256
+// samples of 256^2: 524 us with 4, 500 with 8); with 16 where there are few wavefronts to hide it
+// (24 samples: 131 and 124; 256 samples: 549 and 565); else 4.
+template <int W, int B, bool MULTI, bool DELAY, bool ROWS>
 __global__ void __launch_bounds__(64)
-__attribute__((amdgpu_waves_per_eu(W > 48 ? 1 : (W > 32 || DELAY ? 2 : (W >= 24 ? 3 : 4)), 8)))
+__attribute__((amdgpu_waves_per_eu(W > 32 || DELAY ? 2 : (W >= 24 ? 3 : 4), 8)))
 sf_kernel(const SfArgs a)
 {
     constexpr int BUF = 2 * 64 * kSfPitch;
@@ -437,29 +441,31 @@ sf_kernel(const SfArgs a)
         double* dbuf = lds + (DELAY ? BUF : 0);
         seg[lane] = make_int2(line * n, yr);
         wave_fence();
-        SfRow d{F, R, seg, n, 0, div};
+        using Row = SfRow<B>;
+        Row d{F, R, seg, n, 0, div};
         sf_fill<W>(d, ring, lds);
         seg[lane] = make_int2(line * n, y0);
         wave_fence();
-        SfRow v{F, R, seg, n, 0, div};
-        if (DELAY) d = SfRow{F, R, seg, n, n - shift % n, div};
+        Row v{F, R, seg, n, 0, div};
+        if (DELAY) d = Row{F, R, seg, n, n - shift % n, div};
         if (DELAY && d.y == n) d.y = 0;
-        sf_march<W, MULTI, DELAY>(v, d, lds, dbuf, part == 0, len, a.seg, ring, acc);
+        sf_march<W, B, MULTI, DELAY>(v, d, lds, dbuf, part == 0, len, a.seg, ring, acc);
     } else {
         const int32_t stride = (a.axis == 1) ? a.n[0] : a.n[0] * a.n[1];
         const uint32_t base = (uint32_t)(line / stride) * stride * n + line % stride;
         const uint32_t end = base + n * stride;   // < 2^32: base and span are below 2^31
-        SfColumn v{F, R, stride, n * stride, base + yr * stride, end, div};
+        using Column = SfColumn<B>;
+        Column v{F, R, stride, n * stride, base + yr * stride, end, div};
         sf_fill<W>(v, ring, nullptr);
         v.at = base + y0 * stride;
-        SfColumn d{F, R, stride, n * stride, base + yd * stride, end, div};
-        sf_march<W, MULTI, DELAY>(v, d, nullptr, nullptr, part == 0, len, a.seg, ring, acc);
+        Column d{F, R, stride, n * stride, base + yd * stride, end, div};
+        sf_march<W, B, MULTI, DELAY>(v, d, nullptr, nullptr, part == 0, len, a.seg, ring, acc);
     }
     double* out = a.partial + ((int64_t)b * a.nq + qi) * a.max_h * a.nblk + a.first + unit;
     if constexpr (MULTI) {   // lanes of one part of the lags are 1 << lsplit apart
 #pragma unroll
         for (int l = 0; l < W; ++l) {
-            for (int m = 32; m >= 1 << lsplit; m /= 2) acc[l] = acc[l] + __shfl_xor(acc[l], m);
+            for (int m = 1 << lsplit; m <= 32; m *= 2) acc[l] = acc[l] + __shfl_xor(acc[l], m);
             const int h = a.h0 + part * W + l;
             if (lane == part && h <= a.max_h) out[(int64_t)(h - 1) * a.nblk] = acc[l];
         }
@@ -468,10 +474,136 @@ sf_kernel(const SfArgs a)
         double sum[P];
 #pragma unroll
         for (int l = 0; l < P; ++l) sum[l] = l < W ? acc[l] : 0.0;
-        sf_wave_sum<P / 2, 32>(sum);
-        const int l = lane / (64 / P), h = a.h0 + l;
-        if (lane % (64 / P) == 0 && l < W && h <= a.max_h) out[(int64_t)(h - 1) * a.nblk] = sum[0];
+        sf_wave_sum<P / 2, 1>(sum);
+        const int l = (int)(__brev((unsigned)lane) / (0x80000000u / (P / 2))), h = a.h0 + l;
+        if (lane < P && l < W && h <= a.max_h) out[(int64_t)(h - 1) * a.nblk] = sum[0];
     }
+}
+
+// The same partial sums, bit for bit, for launches of few units. A wavefront of the kernel above is
+// alone on its SIMD there, and takes the segment's cells one after the other for all its lags
+// (256^2, one sample, 37 lags: two launches of 32 wavefronts and 128 steps, 130 us the call). Here a
+// workgroup stages a unit's segments and the cells behind them in LDS, each value formed once, and
+// a thread takes four lags of a segment: the same terms in the same order, and the same tree over
+// the segments. One launch for all axes. 73 us the call; the bound is the chain of loads, steps
+// and sums of one workgroup, and with more of them the two LDS reads for eight operations.
+// LDS: val[cell][segment], cell 0 the one max_h behind the segment's first.
+constexpr int kSfSmallLags = 4;
+constexpr int kSfSmallThreads = 1024;
+
+struct SfSmallArgs {
+    const double* state;   // [batch][nq][cells]
+    int32_t n[3];
+    int64_t cells;
+    int32_t nq, max_h, parts, staged;   // a unit's segments: `parts` times `staged` of them
+    SfPlan p;
+    int32_t div_lo, div_hi;
+    double* partial;       // [batch][nq][max_h][units]
+};
+
+__global__ void __launch_bounds__(kSfSmallThreads) sf_small_kernel(const SfSmallArgs a)
+{
+    constexpr int L = kSfSmallLags, D = 4;
+    extern __shared__ double val[];
+    __shared__ int2 from[64];   // of a segment's line, the first cell; the column of cell 0
+    const int64_t unit = blockIdx.x;
+    const int axis = unit >= a.p.first[2] ? 2 : (unit >= a.p.first[1] ? 1 : 0);
+    const int S = a.staged, parts = a.parts, H = a.max_h;
+    const int pitch = S | 1;   // odd: cells of a line in different banks
+    const int32_t n = a.n[axis], seg = a.p.seg[axis];
+    const int64_t segs = a.p.segs[axis];
+    const uint32_t lines = (uint32_t)(a.cells / n);
+    const uint32_t stride = axis == 0 ? 1u : (axis == 1 ? (uint32_t)a.n[0] : (uint32_t)a.n[0] * (uint32_t)a.n[1]);
+    const int qi = blockIdx.y, b = blockIdx.z;
+    const double* F = a.state + ((int64_t)b * a.nq + qi) * a.cells;
+    const double* R = a.state + (int64_t)b * a.nq * a.cells;
+    const bool div = qi >= a.div_lo && qi < a.div_hi;   // uniform
+    const int s = threadIdx.x & (S - 1), h0 = 1 + (int)(threadIdx.x / S) * L;
+    double sum[L];
+#pragma unroll
+    for (int l = 0; l < L; ++l) sum[l] = 0.0;
+
+#pragma unroll 1
+    for (int part = 0; part < parts; ++part) {
+        const int64_t at0 = ((unit - a.p.first[axis]) * parts + part) * S;
+        if (at0 >= segs) break;   // uniform
+        if (threadIdx.x < (unsigned)S) {
+            const uint32_t at = (uint32_t)(at0 + threadIdx.x < segs ? at0 + threadIdx.x : segs - 1);   // segs < 2^31
+            const uint32_t line = at % lines;
+            from[threadIdx.x] = make_int2((int32_t)(line / stride * stride * n + line % stride),
+                                          wrap_index((int32_t)(at / lines) * seg - H, n, BC_PERIODIC));
+        }
+        __syncthreads();   // and the part before is read
+        // the segments' values: D cells of a segment at a time, `apart` cells from each other, by
+        // lanes along the line for x, across the lines for y and z
+        const int span = seg + H, waves = blockDim.x >> 6, lane = threadIdx.x & 63;
+        const int apart = axis == 0 ? 64 : (int)blockDim.x / S;
+        for (int k = axis == 0 ? (int)threadIdx.x >> 6 : s; k < S; k += axis == 0 ? waves : S) {
+            const int2 f = from[k];
+            for (int c0 = axis == 0 ? lane : (int)threadIdx.x / S; c0 < span; c0 += D * apart) {
+                double v[D], r[D];
+#pragma unroll
+                for (int i = 0; i < D; ++i) {
+                    const int c = c0 + i * apart;
+                    v[i] = r[i] = 1.0;
+                    if (c < span) {
+                        const uint32_t cell = (uint32_t)f.x + (uint32_t)wrap_index(f.y + c, n, BC_PERIODIC) * stride;
+                        v[i] = F[cell];   // cells < 2^31
+                        if (div) r[i] = R[cell];
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < D; ++i) {
+                    const int c = c0 + i * apart;
+                    if (c < span) val[c * pitch + k] = div ? v[i] * (1.0 / r[i]) : v[i];
+                }
+            }
+        }
+        __syncthreads();
+
+        const int64_t want = at0 + s;
+        const int32_t y0 = (int32_t)(want / lines) * seg;
+        const int32_t len = (want >= segs || h0 > H) ? 0 : (n - y0 < seg ? n - y0 : seg);
+        const double* now = val + H * pitch + s;
+        // w[l]: the value h0 + l cells behind (lags beyond max_h: any, and not stored)
+        double w[L], acc[L];
+#pragma unroll
+        for (int l = 0; l < L; ++l) {
+            const int c = H - h0 - l;
+            w[l] = val[(c < 0 ? 0 : c) * pitch + s];
+            acc[l] = 0.0;
+        }
+        for (int y = 0; y < len; y += D) {   // D cells of padding past the last segment's end
+            double v[D], in[D];
+#pragma unroll
+            for (int i = 0; i < D; ++i) {
+                v[i] = now[(y + i) * pitch];
+                in[i] = now[(y + i + 1 - h0) * pitch];
+            }
+#pragma unroll
+            for (int i = 0; i < D; ++i) {
+                if (y + i < len) {
+#pragma unroll
+                    for (int l = 0; l < L; ++l) {
+                        const double d = v[i] - w[l];
+                        acc[l] = __builtin_fma(d, d, acc[l]);
+                    }
+                }
+#pragma unroll
+                for (int l = L - 1; l > 0; --l) w[l] = w[l - 1];
+                w[0] = in[i];
+            }
+        }
+#pragma unroll
+        for (int l = 0; l < L; ++l) {
+            for (int m = 1; m < S; m *= 2) acc[l] = acc[l] + __shfl_xor(acc[l], m);
+            sum[l] = sum[l] + acc[l];   // 0 + the first half + the second
+        }
+    }
+    double* out = a.partial + ((int64_t)b * a.nq + qi) * H * a.p.first[3] + unit;
+#pragma unroll
+    for (int l = 0; l < L; ++l)
+        if (s == 0 && h0 + l <= H) out[(int64_t)(h0 + l - 1) * a.p.first[3]] = sum[l];
 }
 
 // S_q(h) of every sample of the chunk: the unit partials of (sample, quantity, lag) summed and
@@ -673,12 +805,34 @@ void launch_welford(int nf, int kind, const double* state, int64_t cells, int32_
     else welford_launch<5, 1>(state, cells, batch, count0, mean, m2, s);
 }
 
-template <int W, bool MULTI, bool DELAY>
+template <int W, int B, bool MULTI, bool DELAY>
 static void sf_launch(const SfArgs& a, int32_t batch, hipStream_t s)
 {
     const dim3 grid((unsigned)(((a.segs << a.lsplit) + 63) / 64), a.nq, batch), block(64);
-    if (a.axis == 0) hipLaunchKernelGGL((sf_kernel<W, MULTI, DELAY, true>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((sf_kernel<W, MULTI, DELAY, false>), grid, block, 0, s, a);
+    if (a.axis == 0) hipLaunchKernelGGL((sf_kernel<W, B, MULTI, DELAY, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((sf_kernel<W, B, MULTI, DELAY, false>), grid, block, 0, s, a);
+}
+
+// Passes of few units go by sf_small_kernel. us per call, marching -> small (Euler, 2D):
+// one lane per segment, to 1024 units: 256^2, one sample (64 units) 8 lags 95 -> 68, 37 lags
+// 130 -> 73; 8 samples (512) 101 -> 79, 138 -> 96; 16 samples (1024) 110 -> 107, 151 -> 133; 24 samples
+// (1536) 108 -> 130, 154 -> 164;
+// several lanes, to 4096: 64 lags, 256^2, one sample (128) 144 -> 68, 24 samples (3072) 217 -> 181,
+// 32 samples (4096) 226 -> 216, 48 samples (6144) 282 -> 293; 512^2 x 8 (4096) 244 -> 210, x 16 (8192)
+// 335 -> 347; 250 lags, 512^2 x 8 (4096) 612 -> 522, x 16 (8192) 898 -> 975.
+// A unit of 64 segments is staged at once where few units are about or two fit a CU's LDS, else in
+// halves, for three workgroups per CU: 256^2, 37 lags, one sample 73 at once and 84 in halves, 16
+// samples 147 and 133.
+static bool sf_small(const SfPlan& p, int32_t nq, int32_t max_h, int32_t batch, SfSmallArgs& a, size_t& lds)
+{
+    const int64_t units = p.first[3] * nq * batch;
+    if (units > (p.split > 1 ? 4096 : 1024)) return false;
+    const int32_t seg = std::max(p.seg[0], std::max(p.seg[1], p.seg[2]));
+    auto bytes = [&](int staged) { return sizeof(double) * (size_t)(seg + max_h + 4) * (staged | 1); };
+    a.parts = p.split == 1 && units > 512 && bytes(64) > 80 * 1024 ? 2 : 1;
+    a.staged = 64 / p.split / a.parts;
+    lds = bytes(a.staged);
+    return (max_h + kSfSmallLags - 1) / kSfSmallLags * a.staged <= kSfSmallThreads && lds <= 160 * 1024;
 }
 
 void launch_sf_partial(const double* state, int32_t dim, const int32_t n[3], int32_t nq,
@@ -698,20 +852,39 @@ void launch_sf_partial(const double* state, int32_t dim, const int32_t n[3], int
     // divided by field 0
     a.div_lo = kind > 0 ? 1 : 0;
     a.div_hi = kind == 1 ? nq - 1 : (kind == 3 ? 4 : (kind == 2 ? nq : 0));
+    SfSmallArgs b{};
+    size_t lds;
+    if (sf_small(p, nq, max_h, batch, b, lds)) {
+        b.state = state;
+        for (int d = 0; d < 3; ++d) b.n[d] = n[d];
+        b.cells = a.cells;
+        b.nq = nq;
+        b.max_h = max_h;
+        b.p = p;
+        b.div_lo = a.div_lo;
+        b.div_hi = a.div_hi;
+        b.partial = partial;
+        const int tasks = b.staged * ((max_h + kSfSmallLags - 1) / kSfSmallLags);
+        hipLaunchKernelGGL(sf_small_kernel, dim3((unsigned)p.first[3], nq, batch),
+                           dim3(tasks > 512 ? kSfSmallThreads : 512), lds, s, b);
+        return;
+    }
+    const bool few = p.first[3] * nq * batch <= 2048;
     for (a.h0 = 1; a.h0 <= max_h; a.h0 += p.width * p.split) {
         for (a.axis = 0; a.axis < dim; ++a.axis) {
             a.seg = p.seg[a.axis];
             a.segs = p.segs[a.axis];
             a.first = p.first[a.axis];
-            if (a.h0 > 1) sf_launch<32, true, true>(a, batch, s);   // width 32: max_h > 64 * 32
-            else if (p.split > 1 && p.width == 24) sf_launch<24, true, false>(a, batch, s);
-            else if (p.split > 1) sf_launch<32, true, false>(a, batch, s);
-            else if (p.width == 48) sf_launch<48, false, false>(a, batch, s);
-            else if (p.width == 40) sf_launch<40, false, false>(a, batch, s);
-            else if (p.width == 32) sf_launch<32, false, false>(a, batch, s);
-            else if (p.width == 24) sf_launch<24, false, false>(a, batch, s);
-            else if (p.width == 16) sf_launch<16, false, false>(a, batch, s);
-            else sf_launch<8, false, false>(a, batch, s);
+            if (a.h0 > 1) sf_launch<32, 4, true, true>(a, batch, s);   // width 32: max_h > 64 * 32
+            else if (p.split > 1 && p.width == 24) sf_launch<24, 4, true, false>(a, batch, s);
+            else if (p.split > 1) sf_launch<32, 4, true, false>(a, batch, s);
+            else if (p.width == 48) sf_launch<48, 4, false, false>(a, batch, s);
+            else if (p.width == 40) sf_launch<40, 4, false, false>(a, batch, s);
+            else if (p.width == 32) sf_launch<32, 4, false, false>(a, batch, s);
+            else if (p.width == 24) sf_launch<24, 4, false, false>(a, batch, s);
+            else if (p.width == 16 && few) sf_launch<16, 8, false, false>(a, batch, s);
+            else if (p.width == 16) sf_launch<16, 4, false, false>(a, batch, s);
+            else sf_launch<8, 8, false, false>(a, batch, s);
         }
     }
 }
