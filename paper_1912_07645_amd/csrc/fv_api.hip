@@ -1111,15 +1111,13 @@ extern "C" fv_status fv_stats_create(const fv_solver* s, int32_t max_h, fv_stats
     st->max_h = max_h;
     st->nq = s->nf;
     st->count = 0;
-    // samples per pass: with structure functions, a chunk at a time (their partial sums). Without,
-    // the whole batch goes through one Welford launch
-    const int64_t state_bytes = (int64_t)sizeof(double) * st->nq * s->cells;
-    st->chunk = max_h > 0 ? (int32_t)std::max<int64_t>(1, std::min<int64_t>(256, (512ll << 20) / state_bytes))
-                          : (1 << 30);
     const size_t field = sizeof(double) * st->nq * s->cells;
     const size_t lags = sizeof(double) * st->nq * std::max(max_h, 1);
     const int32_t n32[3] = {(int32_t)s->grid.n[0], (int32_t)s->grid.n[1], (int32_t)s->grid.n[2]};
     const int64_t nblk = max_h > 0 ? sf_units(s->grid.dim, n32, max_h) : 0;
+    // samples per pass: with structure functions, a chunk at a time (their partial sums). Without,
+    // the whole batch goes through one Welford launch
+    st->chunk = max_h > 0 ? sf_chunk(s->grid.dim, n32, st->nq, max_h) : (1 << 30);
     bool ok = hipMalloc((void**)&st->mean, field) == hipSuccess &&
               hipMalloc((void**)&st->m2, field) == hipSuccess &&
               hipMalloc((void**)&st->s2mean, lags) == hipSuccess &&

@@ -30,6 +30,8 @@ void launch_mlmc_combine(const CombineArgs& a, double* out, hipStream_t s);
 
 // Partial sums per (sample, quantity, lag) of the structure-function pass.
 int64_t sf_units(int32_t dim, const int32_t n[3], int32_t max_h);
+// Samples whose partial sums (and S_q(h)) are held at a time.
+int32_t sf_chunk(int32_t dim, const int32_t n[3], int32_t nq, int32_t max_h);
 void launch_welford(int nf, int kind, const double* state, int64_t cells, int32_t batch,
                     int64_t count0, double* mean, double* m2, hipStream_t s);
 // The quantities are formed from the state as launch_welford forms them.

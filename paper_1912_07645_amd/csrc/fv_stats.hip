@@ -134,7 +134,8 @@ static SfPlan sf_plan(int32_t dim, const int32_t n[3], int32_t max_h)
     const int32_t w = (max_h + 8 * p.split - 1) / (8 * p.split) * 8, most = p.split > 1 ? 32 : kSfAlone;
     p.width = w < most ? w : most;
     const int64_t cells = (int64_t)n[0] * n[1] * n[2];
-    for (int32_t len = 64 * std::max(2, p.split);; len /= 2) {
+    // twice as long where max_h sums per unit come to more than the field
+    for (int32_t len = 64 * std::max(2, p.split) * ((int64_t)max_h * dim > 8192 ? 2 : 1);; len /= 2) {
         int64_t at = 0;
         for (int d = 0; d < 3; ++d) {
             const int32_t per = (n[d] + len - 1) / len;
@@ -781,6 +782,15 @@ __global__ void fill_zero_kernel(double* __restrict__ p, int64_t n)
 int64_t sf_units(int32_t dim, const int32_t n[3], int32_t max_h)
 {
     return sf_plan(dim, n, max_h).first[3];
+}
+
+// At most 256 samples, 512 MB of states and 1 GB of partial sums (or those of one sample).
+int32_t sf_chunk(int32_t dim, const int32_t n[3], int32_t nq, int32_t max_h)
+{
+    const int64_t state = (int64_t)sizeof(double) * nq * n[0] * n[1] * n[2];
+    const int64_t sums = (int64_t)sizeof(double) * nq * max_h * (sf_units(dim, n, max_h) + 1);
+    const int64_t most = std::min((int64_t(512) << 20) / state, (int64_t(1) << 30) / sums);
+    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(256, most));
 }
 
 template <int NF, int KIND>

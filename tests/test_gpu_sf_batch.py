@@ -13,7 +13,7 @@ from gpu_helpers import note, solver_for, torch_gpu
 pytestmark = pytest.mark.gpu
 
 CASES = [("euler", (17,), 16, 4096), ("euler", (130,), 5, 4096), ("euler", (100,), 48, 2048), ("euler", (100,), 50, 2048),
-         ("euler", (700,), 600, 512), ("euler", (2300,), 2100, 128), ("burgers", (129,), 33, 4096),
+         ("euler", (700,), 600, 512), ("euler", (2300,), 2100, 128), ("euler", (9000,), 8500, 128), ("burgers", (129,), 33, 4096),
          ("euler", (33, 20), 8, 1024), ("euler", (65, 130), 37, 512), ("euler", (256, 40), 24, 512),
          ("euler", (127, 129), 64, 256), ("swe", (70, 65), 40, 512), ("mhd", (40, 66), 17, 256),
          ("euler", (9, 11, 130), 7, 256), ("euler", (20, 70, 18), 16, 256), ("mhd", (30,), 20, 2048)]
