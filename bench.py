@@ -142,7 +142,8 @@ STAGE_KERNEL_COMMON = ("fv_common.h", "fv_physics.h", "fv_fast.h", "fv_registry.
                        "fv_stage_y.h", "fv_stage_z.h")
 STAGE_KERNEL_UNIT = {"kh2d": ("inst_euler2d_hot.hip", "inst_rows2d.hip"),
                      "kh3d": ("inst_euler3d_hot.hip", "inst_planes3d.hip"),
-                     "kh2d_roe": ("inst_more2d.hip",), "swe2d": ("inst_swe.hip",),
+                     "kh2d_roe": ("inst_more2d.hip",),
+                     "swe2d": ("inst_swe.hip", "inst_rows2d.hip"),
                      "kh2d_godunov": ("inst_godunov.hip",), "kh2d_ec4": ("inst_ec.hip",),
                      "mhd2d": ("inst_mhd.hip",)}
 

@@ -409,14 +409,29 @@ struct StepPlan {
 // Whether solvers left to their default run the marching kernel of their scheme: on enough tiles
 // to fill the chip, whose columns are at least four fifths full on every grid. us per step,
 // tile -> march.
-// By rows (2D, a wavefront to a tile; three rounds of the 4096 that fit): WENO3 + HLLC, 256^2 x
-// 256 samples (16384 tiles) 1567 -> 1412, 2048^2 (8192) 364 -> 377; MUSCL + HLL, 256^2 x 256
-// (32768) 820 -> 748, 256^2 x 40 (5120) 133 -> 132, 512^2 x 8 (4096) 106 -> 113. Fewer tiles
-// leave much of the chip idle in the last round.
-// By planes (3D, a workgroup to a tile; 768 fit): WENO3 + HLLC, 64^3 x 8 (640 tiles) 506 -> 474,
-// 128^3 (576) 496 -> 494, 96^3 (252) 235 -> 271, 256^3 (4608) 3322 -> 2527; MUSCL + HLL, 64^3 x 8
-// 285 -> 251, 96^3 128 -> 150, 256^3 2094 -> 1263; 17 x 200 x 200 x 4, its columns half empty,
-// 629 -> 892.
+// By rows (2D, a wavefront to a tile; three rounds of the 4096 that fit):
+//                            256^2 x 256     256^2 at the rule  1024^2 at the rule
+//   WENO3, HLLC              1752 -> 1586    1331 -> 1200       1281 -> 1194
+//   WENO3, HLL               1651 -> 1498    1249 -> 1143       1196 -> 1134
+//   WENO3, Rusanov           1550 -> 1400    1163 -> 1068       1119 -> 1060
+//   MUSCL, HLLC              1508 -> 1347     585 ->  542        562 ->  533
+//   MUSCL, HLL               1381 -> 1270     541 ->  504        521 ->  511
+//   MUSCL, Rusanov           1281 -> 1177     497 ->  462        495 ->  472
+//   shallow water, HLL        781 ->  669     302 ->  258        296 ->  256
+//   shallow water, Rusanov    687 ->  599     267 ->  230        255 ->  231
+// (192 or 96 samples of 256^2, 12 or 6 of 1024^2 are at the rule.) Fewer tiles leave much of the
+// chip idle in the last round: MUSCL + HLL, 256^2 x 40 (5120 tiles) 133 -> 132, 512^2 x 8 (4096)
+// 106 -> 113; WENO3 + HLLC, 2048^2 (8192) 364 -> 377.
+// By planes (3D, a workgroup to a tile; 768 fit):
+//                     64^3 x 8 (640)  128^3 x 2 (1152)  256^3 (4608)
+//   WENO3, HLLC       523 -> 489      1012 -> 771       3742 -> 2855
+//   WENO3, HLL        499 -> 458       987 -> 733       3687 -> 2686
+//   WENO3, Rusanov    466 -> 423       941 -> 682       3522 -> 2499
+//   MUSCL, HLLC       436 -> 400       892 -> 651       3360 -> 2355
+//   MUSCL, HLL        426 -> 366       879 -> 613       3279 -> 2207
+//   MUSCL, Rusanov    405 -> 340       839 -> 564       3172 -> 2022
+// Below: WENO3 + HLLC, 96^3 (252) 235 -> 271; MUSCL + HLL, 96^3 128 -> 150. Columns half empty:
+// 17 x 200 x 200 x 4, MUSCL + HLL, 629 -> 892.
 static bool march_pays(const std::vector<GroupRun>& runs)
 {
     const fv_solver* s0 = runs[0].s;

@@ -133,7 +133,7 @@ struct StageKernel {
 // Registry (filled by the instantiation units).
 const StageKernel* find_stage_kernel(int dim, int eq, int recon, int flux, int variant);
 int num_stage_variants(int dim, int eq, int recon, int flux);
-// The row-marching kernel of a combination, if it has one.
+// The marching kernel of a combination, if it has one.
 const StageKernel* find_march_kernel(int dim, int eq, int recon, int flux);
 
 }  // namespace fvk

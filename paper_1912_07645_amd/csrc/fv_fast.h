@@ -55,14 +55,16 @@ __device__ __forceinline__ double recip48(double d)
 // y[i] = 1/d[i] within half a unit in the last place (2^-97 before its rounding) for N
 // denominators whose product stays in the normal range, from one hardware reciprocal.
 //
-// The rounding step of a quotient then fails for one kind of operands only: a denominator whose
-// 53 bits are all ones, whose reciprocal 2^k (1 + 2^-53 + 2^-106) lies that little above the
-// middle of two numbers, under a numerator that is a power of two. One denominator by itself
-// gets it right, since the hardware estimate does (this is the sequence that a division
-// expands to). SHARP gets it right for several, with a cubic last step: one more operation each,
-// taken where both operands come from the same few values of a nearly uniform flow. A WENO3
-// denominator and its numerator, sums of squares of squares and products with them, meet it by
-// chance only (2^-104).
+// The rounding step of a quotient can then fail where the reciprocal lies within that error of the
+// middle of two numbers and has come out as the wrong one: denominators an odd number of units
+// below a power of two (of all ones, whose reciprocal is 2^k (1 + 2^-53 + 2^-106), to about 30
+// units), under the few numerators whose quotient is next to a middle itself (a power of two
+// under all ones; 0x16666666666663 under 2 - 5 * 2^-52). One denominator by itself gets these
+// right, since the hardware estimate does (this is the sequence that a division expands to).
+// SHARP gets them right for several, with a cubic last step: one more operation each, taken where
+// both operands come from the same few values of a nearly uniform flow. A WENO3 denominator and
+// its numerator, sums of squares of squares and products with them, meet them by chance only
+// (2^-44 for the denominator, times that of the numerator).
 template <int N, bool SHARP = false>
 __device__ __forceinline__ void recips(const double (&d)[N], double (&y)[N])
 {

@@ -43,7 +43,7 @@ struct fv_solver {
     int32_t variant;
     bool variant_set;                      // the caller or the tuner chose it: no choice by size
     int32_t ran = -1;                      // variant of the last stepping call
-    const fvk::StageKernel* march;         // row-marching kernel of the scheme, if it has one
+    const fvk::StageKernel* march;         // marching kernel of the scheme, if it has one
     const fvk::StageKernel* kern;
     // 1D grids small enough for one workgroup: the single-workgroup time loop, offered as
     // the variant after the tiled ones (use_small when it is the selected variant)

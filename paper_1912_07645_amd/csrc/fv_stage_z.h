@@ -5,7 +5,8 @@
 // walks a segment of BZ planes along z, one plane at a time:
 //   * each thread owns one column and keeps the 2G cells of that column that the next z face
 //     reads in registers, so z faces need neither LDS nor re-reads of neighbouring planes; the
-//     z flux on the lower face of a cell is the one the thread computed on the previous plane;
+//     z flux on the lower face of a cell is the one the thread computed on the previous plane,
+//     in an LDS slot of its own;
 //   * only the current plane, with its x and y halo (no corners: faces read axis neighbours
 //     only), is staged in LDS for the x and y faces; the plane's own cells come from the
 //     column registers, so only the halo is loaded from memory for it;
@@ -13,8 +14,9 @@
 //     current plane are computed, so their latency hides behind the arithmetic.
 // A plane of a 16 x 15 block has 255 x faces, 256 y faces (two passes of 256 lanes) and one
 // z face per column. Against a cube tile with a full halo this cuts the cells read per
-// updated cell from (B + 2G)^3 / B^3 (4.6 for B = 6) to about 1.5, and the LDS per workgroup
-// from 40 KB to 36 KB.
+// updated cell from (B + 2G)^3 / B^3 (4.6 for B = 6) to about 1.5. LDS per workgroup (Euler,
+// WENO3): 36 KB for the plane and its faces and 10 KB for the lower z fluxes, three workgroups
+// to a CU as its 168 registers allow; a cube tile of 6 takes 40 KB.
 #pragma once
 
 #include "fv_stage.h"

@@ -90,14 +90,14 @@ welford_kernel(const double* __restrict__ state, int64_t cells, int32_t batch, i
 // A lane takes a segment of a line and marches along it with the last W values in a ring of
 // registers (its indices are compile-time: the march is unrolled by W), so a value is read once
 // and serves W terms, a subtraction and a fused multiply-add each, into W accumulators. With more
-// than 32 lags, `split` neighbouring lanes share a segment (MULTI): each takes W lags, and a value
+// than 48 lags, `split` neighbouring lanes share a segment (MULTI): each takes W lags, and a value
 // that leaves a lane's ring enters the next lane's. Neighbouring segments are the same part of
 // neighbouring lines, then the next part, so wavefronts are full also where lines are few. The sums
 // meet once, at the end. A workgroup is one wavefront (3 to a SIMD at W = 32; with four to a group,
 // whose place is free only when the last ends, 556 us against 512).
 //
-// Lines along y and z: loads four steps ahead. Lines along x: chunks of 8 columns of the
-// wavefront's segments go through LDS (8 lanes a row of 64 bytes), half a chunk ahead.
+// Lines along y and z: loads four or eight steps ahead. Lines along x: chunks of 8 columns of the
+// wavefront's segments go through LDS (8 lanes a row of 64 bytes), half a chunk or one ahead.
 //
 // The bound is partly memory (read once per axis, 537 MB for 256 samples of 256^2 Euler, 4.6 TB/s
 // with 8 lags) and partly FP64 issue (64 instructions per value and lane at W = 32, 120 us). The
@@ -123,8 +123,9 @@ struct SfPlan {
 // of 64, 275 with two of 32), else 2 to 64 lanes of 24 or 32. Segments of up to 128 cells (497 us
 // per pass of 256 samples of 256^2 with 32 lags, against 508 with 64: every segment reads W cells
 // ahead of it, and waits for them), longer ones with many lanes, which keeps the number of partial
-// sums within a small multiple of the field; shorter ones, down to 16, on grids that would have
-// fewer than 16 units. A choice by grid and lags alone: sums do not depend on the batch.
+// sums within a small multiple of the field (256 with two lanes: 64 lags of 64 samples of 256^2 340
+// -> 332 us, of 16 samples 172 -> 228); shorter ones, down to 16, on grids that would have fewer than
+// 16 units. A choice by grid and lags alone: sums do not depend on the batch.
 static SfPlan sf_plan(int32_t dim, const int32_t n[3], int32_t max_h)
 {
     SfPlan p{};
