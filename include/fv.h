@@ -209,7 +209,7 @@ fv_status fv_evolve_multi(int32_t n_groups, fv_solver* const* solvers, double* c
  * profiling (fv_profile_enable) and fv_evolve_multi use the tiled kernels.
  * Until a variant is selected, by fv_set_variant or fv_tune, a solver runs variant 0, except
  * that large 2D batches and large 3D runs take the marching variant of their scheme, if it has
- * one (64 columns by 8 or 16 rows, 16 x 15 columns by 16 planes; listed like the others).
+ * one (64 columns by 8 or 16 rows, 16 x 15 columns by about 16 planes; listed like the others).
  * fv_num_variants returns their number (-1 on NULL); fv_set_variant selects one (FV_EINVAL
  * if out of range); fv_get_tile reports the selected tile shape in cells and its variant
  * index (any output may be NULL); fv_last_variant returns the variant that the solver's last

@@ -374,6 +374,7 @@ static Group make_group(const GroupRun& r, int stage, const StageKernel* kern)
     for (int k = 0; k < 3; ++k) {
         g.n[k] = (int32_t)s->grid.n[k];
         g.tiles[k] = (int32_t)((s->grid.n[k] + tb[k] - 1) / tb[k]);
+        if (k == 2 && kern->march == kMarchPlanes) g.tiles[k] = plane_segments(s->grid.n[k], tb[k]);
         g.ntiles *= g.tiles[k];
     }
     set_divisors(g, g.tiles);
@@ -407,8 +408,8 @@ struct StepPlan {
 };
 
 // Whether solvers left to their default run the marching kernel of their scheme: on enough tiles
-// to fill the chip, whose columns are at least four fifths full on every grid. us per step,
-// tile -> march.
+// to fill the chip, with little room left empty on every grid. us per step, tile -> march.
+//
 // By rows (2D, a wavefront to a tile; three rounds of the 4096 that fit):
 //                            256^2 x 256     256^2 at the rule  1024^2 at the rule
 //   WENO3, HLLC              1752 -> 1586    1331 -> 1200       1281 -> 1194
@@ -421,8 +422,12 @@ struct StepPlan {
 //   shallow water, Rusanov    687 ->  599     267 ->  230        255 ->  231
 // (192 or 96 samples of 256^2, 12 or 6 of 1024^2 are at the rule.) Fewer tiles leave much of the
 // chip idle in the last round: MUSCL + HLL, 256^2 x 40 (5120 tiles) 133 -> 132, 512^2 x 8 (4096)
-// 106 -> 113; WENO3 + HLLC, 2048^2 (8192) 364 -> 377.
-// By planes (3D, a workgroup to a tile; 768 fit):
+// 106 -> 113; WENO3 + HLLC, 2048^2 (8192) 364 -> 377. Strips have to be four fifths full, and what
+// the march walks, a segment costing two rows more than it has, no more than 5/4 of the tiles'
+// room: WENO3 + HLLC, 220 x 30 x 1700 (1.30) 1195 -> 1223, 210 x 57 x 900 (1.24) 1220 -> 1217, 230 x 42 x
+// 1100 (1.14) 1215 -> 1111, 64 x 19 x 6200 (0.72) 1147 -> 820; MUSCL + HLLC, 224 x 60 x 754 (1.45) 884 -> 915.
+//
+// By planes (3D, a workgroup to a tile; 768 fit, three to a CU):
 //                     64^3 x 8 (640)  128^3 x 2 (1152)  256^3 (4608)
 //   WENO3, HLLC       523 -> 489      1012 -> 771       3742 -> 2855
 //   WENO3, HLL        499 -> 458       987 -> 733       3687 -> 2686
@@ -430,26 +435,38 @@ struct StepPlan {
 //   MUSCL, HLLC       436 -> 400       892 -> 651       3360 -> 2355
 //   MUSCL, HLL        426 -> 366       879 -> 613       3279 -> 2207
 //   MUSCL, Rusanov    405 -> 340       839 -> 564       3172 -> 2022
-// Below: WENO3 + HLLC, 96^3 (252) 235 -> 271; MUSCL + HLL, 96^3 128 -> 150. Columns half empty:
+// At 576 tiles, WENO3 + HLLC: 128 x 128 x 64 x 2 467 -> 451, 96 x 90 x 16 x 16 498 -> 455, 64 x 60 x 12 x 36 383 -> 362;
+// 64^3 x 7 (560) 408 -> 452. From 384 tiles where whole segments of 16 and a rest would make 640, that
+// is on thin grids, which fill the cubes of the tile kernel badly: 31 x 14 x 18 x 200 (400, 800)
+// 464 -> 380, 15 x 194 x 17 x 31 (403, 806) 392 -> 360, x 25 (325, 650) 336 -> 358. Columns half empty:
 // 17 x 200 x 200 x 4, MUSCL + HLL, 629 -> 892.
 static bool march_pays(const std::vector<GroupRun>& runs)
 {
     const fv_solver* s0 = runs[0].s;
     const StageKernel* k = s0->march;
     if (!k) return false;
-    int64_t tiles = 0;
+    const bool rows = k->march == kMarchRows;
+    int64_t tiles = 0, whole = 0;   // of the march; by planes, with whole segments and a rest
     for (const GroupRun& r : runs) {
         if (r.s->variant_set) return false;
         const int64_t* n = r.s->grid.n;
         int64_t t[3];
         const int32_t b[3] = {k->bx, k->by, k->bz};
         for (int i = 0; i < 3; ++i) t[i] = (n[i] + b[i] - 1) / b[i];
-        const int64_t across = k->march == kMarchRows ? 1 : n[1];          // columns in use, and
-        const int64_t room = k->march == kMarchRows ? t[0] * b[0] : t[0] * b[0] * t[1] * b[1];
-        if (5 * n[0] * across < 4 * room) return false;                      // columns there are
+        whole += t[0] * t[1] * t[2] * r.batch;
+        if (rows) {
+            const int64_t bx = s0->kern->bx, by = s0->kern->by;
+            const int64_t room = (n[0] + bx - 1) / bx * bx * ((n[1] + by - 1) / by * by);
+            if (5 * n[0] < 4 * t[0] * b[0]) return false;
+            if (4 * t[0] * b[0] * (n[1] + 2 * t[1]) > 5 * room) return false;
+        } else {
+            if (5 * n[0] * n[1] < 4 * (t[0] * b[0] * t[1] * b[1])) return false;
+            t[2] = plane_segments(n[2], b[2]);
+        }
         tiles += t[0] * t[1] * t[2] * r.batch;
     }
-    return tiles >= (k->march == kMarchRows ? 3 * 4096 : 640);
+    if (rows) return tiles >= 3 * 4096;
+    return tiles >= 576 || (tiles >= 384 && whole >= 640);
 }
 
 // Index of a kernel among the variants of the solver's scheme.

@@ -130,6 +130,21 @@ struct StageKernel {
     int32_t march;            // kMarchRows, kMarchPlanes or 0 (a tile at a time)
 };
 
+// Segments of a marching kernel by planes along an axis of n cells. The kernel divides the axis
+// evenly, into segments of at most b planes, or of up to a quarter more where that saves one of
+// segments less than four fifths full: a segment of a plane or two costs a workgroup its start (a
+// column window and a z face) for nothing. us per step (SSP-RK3, WENO3 + HLLC), segments of 16 and
+// the rest -> even ones: 128 x 120 x 34 x 5 samples 594 -> 492 (2 of 17), 47 x 119 x 20 x 27 651 -> 579
+// (1 of 20), 96 x 90 x 98 x 5 788 -> 708 (7 of 14), 250 x 250 x 83 1000 -> 921 (6 of 14), 200 x 161 x 130
+// 769 -> 767 (9 of 15; 8 of 17: 796).
+inline int32_t plane_segments(int64_t n, int32_t b)
+{
+    int64_t t = (n + b - 1) / b;
+    if (t > 1 && 5 * n < 4 * t * b && 4 * ((n + t - 2) / (t - 1)) <= 5 * b) --t;
+    const int64_t len = (n + t - 1) / t;
+    return (int32_t)((n + len - 1) / len);
+}
+
 // Registry (filled by the instantiation units).
 const StageKernel* find_stage_kernel(int dim, int eq, int recon, int flux, int variant);
 int num_stage_variants(int dim, int eq, int recon, int flux);

@@ -2,7 +2,7 @@
 //
 // It computes exactly what the tiled stage kernel computes (same faces, same arithmetic, same
 // order of the x, y, z divergence terms), but a workgroup owns a BX x BY block of columns and
-// walks a segment of BZ planes along z, one plane at a time:
+// walks a segment of about BZ planes along z, one plane at a time:
 //   * each thread owns one column and keeps the 2G cells of that column that the next z face
 //     reads in registers, so z faces need neither LDS nor re-reads of neighbouring planes; the
 //     z flux on the lower face of a cell is the one the thread computed on the previous plane,
@@ -116,9 +116,10 @@ stage_kernel_z(const StageArgs args)
     const int32_t tx = tile % g.tiles[0];
     const int32_t ty = (tile / g.tiles[0]) % g.tiles[1];
     const int32_t tz = tile / (g.tiles[0] * g.tiles[1]);
-    const int32_t x0 = tx * BX, y0 = ty * BY, z0 = tz * BZ;
     const int32_t nx = g.n[0], ny = g.n[1], nz = g.n[2];
-    const int32_t z1 = (z0 + BZ < nz) ? z0 + BZ : nz;
+    const int32_t len = (nz + g.tiles[2] - 1) / g.tiles[2];   // planes of a segment, BZ or about
+    const int32_t x0 = tx * BX, y0 = ty * BY, z0 = tz * len;
+    const int32_t z1 = (z0 + len < nz) ? z0 + len : nz;
     const int64_t cells = g.cells;
     const int32_t plane = nx * ny;   // cells < 2^31: indices within a sample are 32-bit
     const int64_t sbase = (int64_t)sample * NF * cells;

@@ -1,6 +1,6 @@
 """Which kernel a solver left to its default runs, as fv_last_variant reports it, on both sides of the
-size rules: 2D rows from three rounds of 4096 strip segments, 3D planes from 640 tiles, columns at
-least four fifths full; a told variant is kept, by every stepping call."""
+size rules: 2D rows from three rounds of 4096 strip segments, 3D planes from 576 tiles (fewer on thin
+grids), columns at least four fifths full; a told variant is kept, by every stepping call."""
 import numpy as np
 import pytest
 
@@ -58,11 +58,29 @@ def test_rows_by_size(flux, recon):
 
 @pytest.mark.parametrize("flux,recon", SCHEMES)
 def test_planes_by_size(flux, recon):
-    n = (16, 12, 17)                         # one block of columns, four fifths full, of two tiles
+    n = (16, 12, 30)                         # one block of columns, four fifths full, of two tiles
     s = _solver(n, flux, recon)
-    assert _ran(s, n, 319) == 0
-    assert _ran(s, n, 320) == _march(s) > 0
-    assert _ran(_solver((16, 11, 17), flux, recon), (16, 11, 17), 320) == 0
+    assert _ran(s, n, 287) == 0
+    assert _ran(s, n, 288) == _march(s) > 0
+    assert _ran(_solver((16, 11, 30), flux, recon), (16, 11, 30), 320) == 0
+
+
+@pytest.mark.parametrize("n,batch,march", [((220, 30), 1600, False), ((230, 42), 1100, True)])
+def test_rows_not_emptier_than_tiles(n, batch, march):
+    # 256 x (30 + 4) against 5/4 of 224 x 30 cells, and 256 x (42 + 6) against 5/4 of 240 x 45
+    s = _solver(n, "hllc", "weno3")
+    assert _ran(s, n, batch) == (_march(s) if march else 0)
+
+
+@pytest.mark.parametrize("planes,tiles", [(17, 1), (20, 1), (21, 2), (32, 2), (33, 2), (40, 3), (50, 3), (98, 7)])
+def test_plane_segments_are_even(planes, tiles):
+    # 16 x 15 columns: one block; a segment of up to 20 planes where that saves a short one
+    n = (16, 15, planes)
+    s = _solver(n, "hll", "muscl_minmod")
+    whole = -(-planes // 16)
+    batch = min(-(-576 // tiles), max(-(-384 // tiles), -(-640 // whole)))
+    assert _ran(s, n, batch) == _march(s) > 0
+    assert _ran(s, n, batch - 1) == 0
 
 
 def test_no_march_where_there_is_none():
