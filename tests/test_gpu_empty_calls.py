@@ -1,7 +1,7 @@
 """A short run in which no sample takes a step (t is at t_end already) ends after its first decision:
 a call limited to 16 steps costs about what one limited to 2 costs. Each of 14 further steps would add
-at least three launches, 5 us together on this grid, to a call of about 90 us: 1.5 is between 1 and
-the 3 that launching them all measures. And the state, clocks and statuses stay as they are."""
+four launches, 14 us together on this grid, to a call of about 95 us: 1.5 is between 1 and the 3 that
+launching them all measures. And the state, clocks and statuses stay as they are."""
 import time
 
 import numpy as np
